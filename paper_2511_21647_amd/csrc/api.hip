@@ -26,6 +26,7 @@ hipError_t launch_sim(const ulm_ctx *ctx, const double *pos, const double *amp, 
                       uint64_t seed, double noise_sigma, float *iq, const double *angles_dev,
                       hipStream_t st);
 size_t ncc_lds_bytes(int nu, int half);
+int ncc_band_rows(int n_img, int nz);
 hipError_t launch_frame_max(const float2 *P, float *fmax, int n_img, int npix, hipStream_t st);
 size_t cnn_workspace_bytes(int B, int H, int W, bool fp32, bool train);
 size_t pair_workspace_bytes(int planes, int F, int capacity);
@@ -130,8 +131,9 @@ static void layout_workspace(ulm_ctx *ctx) {
     const int nblk = cdiv(c.n_frames, kGramBlock);
     w.gram_pairs = nblk * (nblk + 1) / 2;
     w.gram_chunks = cdiv((int)npix, kGramChunk);
-    w.bands = cdiv(c.nz, kNccBand);
-    w.band_cap = cdiv(kNccBand, 2) * cdiv(c.nu, 2);
+    w.band_rows = ncc_band_rows((int)(planes * F), c.nz);
+    w.bands = cdiv(c.nz, w.band_rows);
+    w.band_cap = cdiv(w.band_rows, 2) * cdiv(c.nu, 2);
     const size_t cc = std::max(1, c.svd_cutoff);
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -168,8 +170,11 @@ static void layout_workspace(ulm_ctx *ctx) {
     w.bar = take(sizeof(int) * planes * kBarStride);
     w.eflag = take(sizeof(int) * planes);
     w.fmax = take(sizeof(float) * planes * F);
+    w.band_max = take(sizeof(float) * planes * F * w.bands);
     w.band_cnt = take(sizeof(int) * planes * F * w.bands);
     w.band_off = take(sizeof(int) * planes * F * w.bands);
+    w.img_cnt = take(sizeof(int) * planes * F);
+    w.img_off = take(sizeof(int) * planes * F);
     w.staged = take(sizeof(ulm_loc_t) * planes * F * w.bands * w.band_cap);
     w.status = take(sizeof(int) * 4);
     w.total = off;

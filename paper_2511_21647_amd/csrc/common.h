@@ -23,7 +23,6 @@ constexpr int kGramBlock = 64;     // frames per Gram block (rows and columns)
 constexpr int kGramChunk = 2048;   // pixels reduced by one Gram work-group
 constexpr int kGramStage = 32;     // pixels staged in LDS per step
 
-constexpr int kNccBand = 16;       // NCC output rows per work-group
 constexpr int kNccMaxHalf = 7;     // template half-width limit (size <= 15)
 
 // Split-precision clutter filter: BF16 terms per operand (x = hi + mid + lo),
@@ -127,12 +126,15 @@ struct Workspace {
     size_t bar;         // [planes][kBarStride] i32 grid-barrier flags + XCC mask
     size_t eflag;       // [planes] i32
     size_t fmax;        // [planes][F] f32
-    size_t band_cnt;    // [planes][F][bands] i32
-    size_t band_off;    // [planes][F][bands] i32
-    size_t staged;      // [planes][F][bands][cap] ulm_loc_t
+    size_t band_max;    // [planes][F][bands] f32   envelope maxima
+    size_t band_cnt;    // [planes][F][bands] i32   regional maxima staged
+    size_t band_off;    // [planes][F][bands] i32   records before the band within its image
+    size_t img_cnt;     // [planes][F] i32          records
+    size_t img_off;     // [planes][F] i32
+    size_t staged;      // [planes][F][bands][cap] regional maxima (32 bytes each)
     size_t status;      // i32
     size_t total;
-    int gram_pairs, gram_chunks, bands, band_cap;
+    int gram_pairs, gram_chunks, bands, band_rows, band_cap;
 };
 
 template <typename T> __host__ __device__ inline T cdiv(T a, T b) { return (a + b - 1) / b; }
