@@ -8,8 +8,8 @@
 // y lies in slab b, and their x must lie in the YZ record's slab.
 //
 //   pair_bounds_kernel  record range of every (plane, frame) in the sorted list
-//   pair_best_kernel    every record's best candidate (one work-group per
-//                       (frame, plane))
+//   pair_order_kernel   whether each range is in row order
+//   pair_best_kernel    every record's best candidate (one thread per record)
 //   pair_count_kernel   mutual pairs per (frame, XZ plane)
 //   launch_scan         their offsets, XZ planes fastest (the localisers' scan)
 //   pair_write_kernel   the pairs of each (frame, XZ plane); records are sorted by
@@ -22,11 +22,16 @@
 
 namespace ulm {
 
+// Record range [2 key], [2 key + 1] of a (plane, frame); the top bit of the second
+// word marks a range whose records are not in row order (see pair_order_kernel).
+constexpr int kPairUnordered = INT32_MIN;
+
 struct PairArgs {
     const ulm_loc_t *locs;
-    int n;                  // records in use: min(count, capacity)
+    const int *count;       // records written; min(count, capacity) are used
+    int capacity;
     int F, B, per;          // frames, slabs per orientation, slab width in pixels
-    const int *bounds;      // [2B][F][2]
+    int *bounds;            // [2B][F][2]
     int *best;              // [n]
     int *cnt, *off;         // [F][B]
 };
@@ -57,6 +62,25 @@ __global__ void pair_bounds_kernel(const ulm_loc_t *__restrict__ locs, const int
     bounds[2 * key + 1] = lower(key + 1);
 }
 
+// A record's candidates lie within one pixel axially, so in a range that is sorted by
+// row (as the localisers write it), with every z within half a pixel of its row, they
+// are a short run.  One pass over the list marks the ranges where that does not hold.
+__global__ __launch_bounds__(256) void pair_order_kernel(PairArgs a, int nkeys)
+{
+    const int n = min(*a.count, a.capacity);
+    for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
+        const int4 w = *reinterpret_cast<const int4 *>(&a.locs[r]);
+        const int key = w.x * a.F + w.y;
+        if (key < 0 || key >= nkeys) continue;
+        bool bad = !(fabsf(a.locs[r].z - (float)w.z) <= 0.5f) || abs(w.z) > (1 << 20);
+        if (r + 1 < n) {
+            const int4 x = *reinterpret_cast<const int4 *>(&a.locs[r + 1]);
+            bad |= x.x * a.F + x.y == key && x.z < w.z;
+        }
+        if (bad) atomicOr(&a.bounds[2 * key + 1], kPairUnordered);
+    }
+}
+
 // cost of pairing an XZ record with a YZ record, each given as (z, u, ncc,
 // intensity), or +inf if they are not candidates (the slab test is separate)
 __device__ inline float pair_cost(float4 xz, float4 yz) {
@@ -72,38 +96,56 @@ __device__ inline float4 loc_zuni(const ulm_loc_t *locs, int r) {
     return *reinterpret_cast<const float4 *>(&locs[r].z);
 }
 
-__global__ __launch_bounds__(256) void pair_best_kernel(PairArgs a)
+// One thread per record, a fixed grid over the list (balanced whatever the number of
+// records per frame).  In a range in row order the scan starts at the first record
+// of row floor(z - 1.75), found by bisection, and ends past row ceil(z + 1.75): five
+// rows of the plane instead of all of them (the margin of 0.25 covers the FP32
+// rounding of |z_i - z_j| <= 1).  Bound by the latency of the bisection's dependent
+// loads; a whole-range scan read every record of the other plane's frame.
+__global__ __launch_bounds__(256) void pair_best_kernel(PairArgs a, int nkeys)
 {
-    const int f = blockIdx.x, p = blockIdx.y;
-    const int lo = a.bounds[2 * (p * a.F + f)], hi = a.bounds[2 * (p * a.F + f) + 1];
-    const bool xz = p < a.B;
-    // with slabs, a candidate's u must lie in this plane's slab; the record's own
-    // u picks the one segment of the other orientation that can hold its partner
-    const int want = xz ? p : p - a.B;
-    for (int r = lo + threadIdx.x; r < hi; r += blockDim.x) {
-        const float4 me = loc_zuni(a.locs, r);
-        int q;
-        if (a.B == 1) {
-            q = xz ? 1 : 0;
-        } else {
-            const int sl = slab_of(me.y, a.per);
-            if (sl < 0 || sl >= a.B) {       // outside every slab: no partner
-                a.best[r] = -1;
-                continue;
-            }
-            q = xz ? a.B + sl : sl;
-        }
-        const int clo = a.bounds[2 * (q * a.F + f)], chi = a.bounds[2 * (q * a.F + f) + 1];
-        float bc = INFINITY;
+    const int n = min(*a.count, a.capacity);
+    for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
+        const int2 pf = *reinterpret_cast<const int2 *>(&a.locs[r]);
+        const int key = pf.x * a.F + pf.y;
         int bi = -1;
-#pragma unroll 4
-        for (int c = clo; c < chi; ++c) {
-            const float4 o = loc_zuni(a.locs, c);
-            float cost = xz ? pair_cost(me, o) : pair_cost(o, me);
-            if (a.B > 1 && slab_of(o.y, a.per) != want) cost = INFINITY;
-            if (cost < bc) {            // strict: the first (smallest index) minimum wins
-                bc = cost;
-                bi = c;
+        if (key >= 0 && key < nkeys) {
+            const int p = key / a.F, f = key - p * a.F;
+            const bool xz = p < a.B;
+            // with slabs, a candidate's u must lie in this plane's slab; the record's own
+            // u picks the one segment of the other orientation that can hold its partner
+            const int want = xz ? p : p - a.B;
+            const float4 me = loc_zuni(a.locs, r);
+            int q = xz ? 1 : 0;
+            if (a.B > 1) {
+                const int sl = slab_of(me.y, a.per);
+                q = sl < 0 || sl >= a.B ? -1 : (xz ? a.B + sl : sl);   // outside every slab: no partner
+            }
+            if (q >= 0) {
+                int clo = a.bounds[2 * (q * a.F + f)], chi = a.bounds[2 * (q * a.F + f) + 1];
+                int last_row = INT32_MAX;
+                if (chi & kPairUnordered) {
+                    chi &= ~kPairUnordered;
+                } else if (fabsf(me.x) < 1e6f) {
+                    const int first_row = (int)floorf(me.x - 1.75f);
+                    last_row = (int)ceilf(me.x + 1.75f);
+                    int hi = chi;
+                    while (clo < hi) {
+                        const int mid = (clo + hi) >> 1;
+                        if (a.locs[mid].iz < first_row) clo = mid + 1; else hi = mid;
+                    }
+                }
+                float bc = INFINITY;
+                for (int c = clo; c < chi; ++c) {
+                    if (a.locs[c].iz > last_row) break;
+                    const float4 o = loc_zuni(a.locs, c);
+                    float cost = xz ? pair_cost(me, o) : pair_cost(o, me);
+                    if (a.B > 1 && slab_of(o.y, a.per) != want) cost = INFINITY;
+                    if (cost < bc) {            // strict: the first (smallest index) minimum wins
+                        bc = cost;
+                        bi = c;
+                    }
+                }
             }
         }
         a.best[r] = bi;
@@ -113,7 +155,7 @@ __global__ __launch_bounds__(256) void pair_best_kernel(PairArgs a)
 __global__ __launch_bounds__(256) void pair_count_kernel(PairArgs a)
 {
     const int f = blockIdx.x, p = blockIdx.y;
-    const int lo = a.bounds[2 * (p * a.F + f)], hi = a.bounds[2 * (p * a.F + f) + 1];
+    const int lo = a.bounds[2 * (p * a.F + f)], hi = a.bounds[2 * (p * a.F + f) + 1] & ~kPairUnordered;
     int c = 0;
     for (int r = lo + threadIdx.x; r < hi; r += blockDim.x) {
         const int j = a.best[r];
@@ -133,7 +175,7 @@ __global__ __launch_bounds__(256) void pair_write_kernel(PairArgs a, ulm_loc3d_t
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     __shared__ int wave_tot[4];
     int base = a.off[f * a.B + p];
-    const int lo = a.bounds[2 * (p * a.F + f)], hi = a.bounds[2 * (p * a.F + f) + 1];
+    const int lo = a.bounds[2 * (p * a.F + f)], hi = a.bounds[2 * (p * a.F + f) + 1] & ~kPairUnordered;
     for (int r0 = lo; r0 < hi; r0 += blockDim.x) {
         const int r = r0 + threadIdx.x;
         int j = -1;
@@ -190,7 +232,8 @@ hipError_t launch_pairing(const ulm_ctx *ctx, const ulm_loc_t *locs, const int *
                        capacity, nkeys, F, bounds);
     PairArgs a;
     a.locs = locs;
-    a.n = capacity;
+    a.count = count;
+    a.capacity = capacity;
     a.F = F;
     a.B = g.n_blocks;
     a.per = cdiv(ctx->cfg.nv, g.n_blocks);
@@ -198,7 +241,10 @@ hipError_t launch_pairing(const ulm_ctx *ctx, const ulm_loc_t *locs, const int *
     a.best = best;
     a.cnt = cnt;
     a.off = off;
-    hipLaunchKernelGGL(pair_best_kernel, dim3(F, planes), dim3(256), 0, st, a);
+    // eight work-groups per CU walk the list
+    const int wgs = std::max(1, std::min(2048, cdiv(capacity, 256)));
+    hipLaunchKernelGGL(pair_order_kernel, dim3(wgs), dim3(256), 0, st, a, nkeys);
+    hipLaunchKernelGGL(pair_best_kernel, dim3(wgs), dim3(256), 0, st, a, nkeys);
     hipLaunchKernelGGL(pair_count_kernel, dim3(F, B), dim3(256), 0, st, a);
     hipError_t e = launch_scan(cnt, off, F * B, out_count, st);
     if (e != hipSuccess) return e;
