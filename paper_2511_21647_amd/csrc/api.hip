@@ -130,7 +130,14 @@ static void layout_workspace(ulm_ctx *ctx) {
     const size_t F = c.n_frames, planes = 2 * (size_t)c.n_blocks, npix = (size_t)c.nz * c.nu;
     const int nblk = cdiv(c.n_frames, kGramBlock);
     w.gram_pairs = nblk * (nblk + 1) / 2;
-    w.gram_chunks = cdiv((int)npix, kGramChunk);
+    // A chunk's pixels are a serial chain of stages (3.7 us per 32 pixels), so where
+    // whole chunks would leave CUs idle they are halved until there are 512
+    // work-groups or a chunk is two stages; the partial sums stay under 70 MB.
+    w.gram_chunk_px = kGramChunk;
+    while (w.gram_chunk_px > 2 * kGramStage &&
+           planes * w.gram_pairs * cdiv(npix, (size_t)w.gram_chunk_px) < 512)
+        w.gram_chunk_px /= 2;
+    w.gram_chunks = cdiv((int)npix, w.gram_chunk_px);
     w.band_rows = ncc_band_rows((int)(planes * F), c.nz);
     w.bands = cdiv(c.nz, w.band_rows);
     w.band_cap = cdiv(w.band_rows, 2) * cdiv(c.nu, 2);

@@ -20,7 +20,7 @@ constexpr int kFirMaxTaps = 48;
 constexpr int kFirGroup = 4;       // slabs per stage-2 work-group (many-slab projections)
 
 constexpr int kGramBlock = 64;     // frames per Gram block (rows and columns)
-constexpr int kGramChunk = 2048;   // pixels reduced by one Gram work-group
+constexpr int kGramChunk = 2048;   // pixels reduced by one Gram work-group at most
 constexpr int kGramStage = 32;     // pixels staged in LDS per step
 
 constexpr int kNccMaxHalf = 7;     // template half-width limit (size <= 15)
@@ -134,7 +134,7 @@ struct Workspace {
     size_t staged;      // [planes][F][bands][cap] regional maxima (32 bytes each)
     size_t status;      // i32
     size_t total;
-    int gram_pairs, gram_chunks, bands, band_rows, band_cap;
+    int gram_pairs, gram_chunks, gram_chunk_px, bands, band_rows, band_cap;
 };
 
 template <typename T> __host__ __device__ inline T cdiv(T a, T b) { return (a + b - 1) / b; }

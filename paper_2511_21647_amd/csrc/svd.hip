@@ -43,7 +43,8 @@ __device__ inline void pair_of(int pair, int nblk, int &I, int &J) {
 // summation rounds.
 __global__ __launch_bounds__(256) void gram_f64_kernel(const float2 *__restrict__ P,
                                                        double2 *__restrict__ part, int F,
-                                                       int npix, int pairs, int chunks, int nblk)
+                                                       int npix, int pairs, int chunks, int chunk_px,
+                                                       int nblk)
 {
     // the block pairs of one pixel chunk run back to back on one XCD, so the
     // frame blocks they share are read from that XCD's L2
@@ -54,8 +55,8 @@ __global__ __launch_bounds__(256) void gram_f64_kernel(const float2 *__restrict_
     int I, J;
     pair_of(pair, nblk, I, J);
     const float2 *src = P + (size_t)plane * F * npix;
-    const int px0 = chunk * kGramChunk;
-    const int px1 = min(px0 + kGramChunk, npix);
+    const int px0 = chunk * chunk_px;
+    const int px1 = min(px0 + chunk_px, npix);
 
     __shared__ float2 lds[2 * kGramBlock][kGramStage + 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -226,7 +227,7 @@ constexpr int kG16Rows = 2 * kGramBlock;         // frames of the two blocks
 __global__ __launch_bounds__(256, 2) void gram_bf16x3_kernel(const float2 *__restrict__ P,
                                                              double2 *__restrict__ part, int F,
                                                              int npix, int pairs, int chunks,
-                                                             int nblk)
+                                                             int chunk_px, int nblk)
 {
     constexpr int NT = kSplitTerms;
     // block pairs of one pixel chunk back to back on one XCD (shared frame blocks in its L2)
@@ -237,8 +238,8 @@ __global__ __launch_bounds__(256, 2) void gram_bf16x3_kernel(const float2 *__res
     int I, J;
     pair_of(pair, nblk, I, J);
     const float2 *src = P + (size_t)plane * F * npix;
-    const int px0 = chunk * kGramChunk;
-    const int px1 = min(px0 + kGramChunk, npix);
+    const int px0 = chunk * chunk_px;
+    const int px1 = min(px0 + chunk_px, npix);
 
     // [buffer][re terms 0..NT-1, im terms 0..NT-1][row][pixel]
     __shared__ __attribute__((aligned(16))) __bf16 lds[2][2 * NT][kG16Rows][kG16Pitch];
@@ -1152,10 +1153,10 @@ hipError_t launch_filter(const ulm_ctx *ctx, float2 *proj, double *eigvals_out, 
     const int nwg = planes * w.gram_pairs * w.gram_chunks;
     if (ctx->cfg.precision == ULM_PREC_BF16X3)
         hipLaunchKernelGGL(gram_bf16x3_kernel, dim3(nwg), dim3(256), 0, st, proj, part, F, npix,
-                           w.gram_pairs, w.gram_chunks, nblk);
+                           w.gram_pairs, w.gram_chunks, w.gram_chunk_px, nblk);
     else
         hipLaunchKernelGGL(gram_f64_kernel, dim3(nwg), dim3(256), 0, st, proj, part, F, npix,
-                           w.gram_pairs, w.gram_chunks, nblk);
+                           w.gram_pairs, w.gram_chunks, w.gram_chunk_px, nblk);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(gram_reduce_kernel, dim3(planes * w.gram_pairs * (kGramBlock / kReduceRows)),
