@@ -18,6 +18,11 @@ constexpr int kFirTileU = 32;
 static_assert(8 * (256 / kFirTileU) == kFirTileZ, "stage-2 tile: 8 rows per thread");
 constexpr int kFirMaxTaps = 48;
 constexpr int kFirGroup = 4;       // slabs per stage-2 work-group (many-slab projections)
+constexpr int kSlabGroup = 5;      // the same where every slab has few taps
+constexpr int kSlabRows = 8;       // output rows per thread there
+constexpr int kSlabMaxTaps = 4;
+constexpr int kSlabSpan = 8;       // rows of the group's union of tap ranges: narrow slabs,
+constexpr int kSlabMaxSpan = 16;   // and the limit
 
 constexpr int kGramBlock = 64;     // frames per Gram block (rows and columns)
 constexpr int kGramChunk = 2048;   // pixels reduced by one Gram work-group at most
@@ -93,7 +98,8 @@ struct Tables {
     int2 *tap_meta;    // [K][B]    (first tap offset, number of taps)
     double *angles;    // [K]       steering angles (simulator)
     int n_taps;        // maximum taps over (transmit, block)
-    int fir_group;     // slabs per stage-2 work-group: 1 or kFirGroup
+    int fir_span;      // rows of the group's union of tap ranges
+    int fir_group;     // slabs per stage-2 work-group: 1, kFirGroup or kSlabGroup
     float2 *sep_tw;    // MB-separation FFT twiddles for F frames (null if F has a factor > 7)
     int *xd_n;         // [K][Nu] cross projection: integer part of the axial shift of column i
     float4 *xd_w;      // [K][Nu] ((1 - frac) e, frac e), e = the column's stage-2 phase
