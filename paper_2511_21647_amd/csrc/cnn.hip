@@ -43,8 +43,7 @@ __host__ __device__ constexpr int off_wh() { return kW0 + kB0 + (kL - 1) * (kWl 
 __host__ __device__ constexpr int off_bh() { return off_wh() + kWh; }
 
 constexpr int kTileRows = 4, kTileCols = 32;   // conv tile: one 32-pixel row per wave
-constexpr int kHeadPx = 128;                   // pixels per head-gradient chunk
-constexpr int kMaxPartials = 256;              // work-groups of a weight-gradient pass
+constexpr int kMaxPartials = 256;              // work-groups of a weight-gradient pass (one per CU)
 
 typedef __bf16 bf16;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -999,27 +998,6 @@ __global__ void cnn_target_kernel(const float2 *__restrict__ mb, const int *__re
     }
 }
 
-// per-block loss partial sums and the logit gradient g = 2 (h - T) / count
-__global__ __launch_bounds__(256) void cnn_loss_kernel(const float *__restrict__ logits,
-                                                       const int *__restrict__ T,
-                                                       float *__restrict__ g, size_t count,
-                                                       double *__restrict__ part)
-{
-    double s = 0.0;
-    const double scale = 2.0 / (double)count;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-         i += (size_t)gridDim.x * blockDim.x) {
-        const float d = logits[i] - __int_as_float(T[i]);
-        s += (double)d * d;
-        g[i] = (float)(scale * d);
-    }
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    __shared__ double red[4];
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
-}
-
 __global__ void cnn_loss_final_kernel(const double *__restrict__ part, int n, double inv_count,
                                       float *__restrict__ loss)
 {
@@ -1035,183 +1013,420 @@ __global__ void cnn_loss_final_kernel(const double *__restrict__ part, int n, do
     }
 }
 
-// head backward, per pixel: dz6[c] = (sum_k wh[k][c] g[k]) where a6[c] > 0, else 0
+// The head in training, forward and backward in one pass over the last activations
+// and the target: logits h = bh + wh a6 (never stored), the loss, g = 2 (h - T) /
+// count, the data gradient dz6[c] = (sum_k wh[k][c] g[k] where a6[c] > 0), and the
+// weight and bias gradients sum_px g[k] a6[c] and sum_px g[k].
+// A wave takes 32 pixels at a time.  The logits come out with the lane holding one
+// k and 16 pixels in registers (head_group's product from LDS), which is where the
+// target is read 128 bytes a pixel and what the weight gradient's A operand needs;
+// g goes through LDS once to put the pixel in the lane for the data gradient.  Both
+// gradients are products on v_mfma_f32_32x32x2f32: g stays in FP32.  A K-step takes
+// index 8 a + b of the lower half-wave and 8 a + 4 + b of the upper, the order in
+// which a result's registers hold its rows.
+// Bound by HBM (target 256 B, activations 64 B read and 64 B written a pixel in
+// BF16) and by the 4100 cycles of FP32 matrix products per 32 pixels, about alike.
+// As five kernels (logits and g through HBM, the weight gradient with one FMA per
+// LDS read) it took 1.7 ms on 16 images of 250 x 274.
+constexpr int kHtGs = kR2 + 4;                  // floats per pixel of g in LDS
+constexpr int kHtWaves = 4;
+constexpr int kHtPart = kWh + 2 * 64;           // raw partial: 32 accumulators and 2 biases per lane
+
 template <typename T>
-__global__ __launch_bounds__(256) void cnn_head_bwd_data_kernel(const float *__restrict__ g,
-                                                                const float *__restrict__ p,
-                                                                const T *__restrict__ a6,
-                                                                T *__restrict__ dz6, size_t npx)
+__global__ __launch_bounds__(64 * kHtWaves, 2) void cnn_head_train_kernel(
+    const T *__restrict__ a6, const float *__restrict__ p, const int *__restrict__ target,
+    T *__restrict__ dz6, float *__restrict__ part, double *__restrict__ lpart, size_t npx)
 {
-    __shared__ float wh[kR2][kC];
-    for (int e = threadIdx.x; e < kR2 * kC; e += blockDim.x) wh[e / kC][e % kC] = p[off_wh() + e];
+    constexpr int PS = Lds<T>::px;
+    __shared__ __attribute__((aligned(16))) T whs[kR2 * Lds<T>::wh];
+    __shared__ float bhs[kR2];
+    __shared__ __attribute__((aligned(16))) T as_all[kHtWaves][32 * PS];
+    __shared__ __attribute__((aligned(16))) float gs_all[kHtWaves][32 * kHtGs];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i32 = lane & 31, hk = lane >> 5;
+    stage_head<T>(p, whs, bhs);
     __syncthreads();
-    const size_t px = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (px >= npx) return;
-    float acc[kC];
+    T *as = as_all[wave];
+    float *gs = gs_all[wave];
+    const double scale = 2.0 / (double)(npx * kR2);
+    // A operand of the data gradient: wh[k][c = lane], k = 32 nb + 8 a + 4 hk + b
+    float wt[2][16];
 #pragma unroll
-    for (int c = 0; c < kC; ++c) acc[c] = 0.f;
-    const float4 *gs = reinterpret_cast<const float4 *>(g + px * kR2);
-    for (int k4 = 0; k4 < kR2 / 4; ++k4) {
-        const float4 v = gs[k4];
-        const float gv[4] = {v.x, v.y, v.z, v.w};
+    for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int q = 0; q < 16; ++q)
+            wt[nb][q] = p[off_wh() + (32 * nb + 8 * (q >> 2) + 4 * hk + (q & 3)) * kC + i32];
+    f32x16 dw[2] = {{}, {}};
+    float db[2] = {0.f, 0.f};
+    double loss = 0.0;
+    const size_t chunks = (npx + 31) / 32;
+    const int nw = gridDim.x * kHtWaves;
+    for (size_t ch = (size_t)blockIdx.x * kHtWaves + wave; ch < chunks; ch += nw) {
+        const size_t p0 = ch * 32;
+        const int np = (int)std::min((size_t)32, npx - p0);
+        // the chunk's activations, zeros past the last pixel
+        constexpr int VEC = 16 / (int)sizeof(T), NV = 32 * kC / VEC;
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int c = 0; c < kC; ++c) acc[c] = fmaf(wh[k4 * 4 + i][c], gv[i], acc[c]);
-    }
+        for (int e = lane; e < NV; e += 64) {
+            const int r = e / (kC / VEC), g = e % (kC / VEC);
+            T v[VEC] = {};
+            if (r < np) *reinterpret_cast<uint4 *>(v) = *reinterpret_cast<const uint4 *>(a6 + (p0 + r) * kC + g * VEC);
 #pragma unroll
-    for (int c = 0; c < kC; ++c) {
-        const bool on = tof(a6[px * kC + c]) > 0.f;
-        dz6[px * kC + c] = fromf<T>(on ? acc[c] : 0.f);
-    }
-}
-
-// Head weight-gradient partials.  Work-group w takes the 128-pixel chunks
-// w, w + G, ...; thread t owns (k, c) = ((t + 256 m) / 32, t % 32), m < 8, and
-// the bias k = t for t < 64.  part[w][k][c] then part[w][2048 + k].
-template <typename T>
-__global__ __launch_bounds__(256) void cnn_head_bwd_weight_kernel(const float *__restrict__ g,
-                                                                  const T *__restrict__ a6,
-                                                                  float *__restrict__ part, size_t npx)
-{
-    __shared__ float gs[kHeadPx][kR2 + 1];
-    __shared__ float as[kHeadPx][kC + 1];
-    const int t = threadIdx.x;
-    float acc[8] = {}, accb = 0.f;
-    const size_t nchunks = (npx + kHeadPx - 1) / kHeadPx;
-    for (size_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
-        const size_t p0 = ch * kHeadPx;
-        const int np = (int)std::min((size_t)kHeadPx, npx - p0);
-        __syncthreads();
-        for (int e = t; e < kHeadPx * kR2; e += 256) {
-            const int r = e / kR2, k = e % kR2;
-            gs[r][k] = r < np ? g[(p0 + r) * kR2 + k] : 0.f;
+            for (int i = 0; i < VEC; ++i) as[r * PS + g * VEC + i] = v[i];
         }
-        for (int e = t; e < kHeadPx * kC; e += 256) {
-            const int r = e / kC, c = e % kC;
-            as[r][c] = r < np ? tof(a6[(p0 + r) * kC + c]) : 0.f;
-        }
-        __syncthreads();
-        const int c = t % kC;
-        for (int r = 0; r < np; ++r) {
-            const float a = as[r][c];
+        int tg[2][16];
 #pragma unroll
-            for (int m = 0; m < 8; ++m) acc[m] = fmaf(gs[r][(t + 256 * m) / kC], a, acc[m]);
-            if (t < kR2) accb += gs[r][t];
-        }
-    }
-    float *dst = part + (size_t)blockIdx.x * (kWh + kBh);
+        for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-    for (int m = 0; m < 8; ++m) dst[t + 256 * m] = acc[m];
-    if (t < kR2) dst[kWh + t] = accb;
-}
-
-// Conv weight-gradient partials (layers 1..5).  Work-group w takes tiles
-// w, w + G, ... of 4 x 32 pixels; thread t owns the pairs (o, c) =
-// ((t + 256 m) / 32, t % 32), m < 4, for all 9 taps, and the bias o = t for t < 32.
-// part[w][o][c][tap] then part[w][9216 + o].
-template <typename T>
-__global__ __launch_bounds__(256) void cnn_conv_bwd_weight_kernel(const T *__restrict__ x,
-                                                                  const T *__restrict__ dz,
-                                                                  float *__restrict__ part, int H,
-                                                                  int W, int B)
-{
-    constexpr int TC = kTileCols + 2;
-    __shared__ float xs[kTileRows + 2][TC][kC + 1];
-    __shared__ float ds[kTileRows][kTileCols][kC + 1];
-    const int t = threadIdx.x, c = t % kC;
-    const int tx = cdiv(W, kTileCols), ty = cdiv(H, kTileRows);
-    const long ntiles = (long)tx * ty * B;
-    float acc[4][9] = {};
-    float accb = 0.f;
-    for (long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int n = tile / ((long)tx * ty), y0 = (tile / tx) % ty * kTileRows,
-                  x0 = tile % tx * kTileCols;
-        __syncthreads();
-        for (int e = t; e < (kTileRows + 2) * TC * kC; e += 256) {
-            const int cc = e % kC, px = (e / kC) % TC, ry = e / (kC * TC);
-            const int yy = y0 + ry - 1, xx = x0 + px - 1;
-            xs[ry][px][cc] = (yy >= 0 && yy < H && xx >= 0 && xx < W)
-                                 ? tof(x[(((size_t)n * H + yy) * W + xx) * kC + cc]) : 0.f;
-        }
-        for (int e = t; e < kTileRows * kTileCols * kC; e += 256) {
-            const int cc = e % kC, px = (e / kC) % kTileCols, ry = e / (kC * kTileCols);
-            const int yy = y0 + ry, xx = x0 + px;
-            ds[ry][px][cc] = (yy < H && xx < W) ? tof(dz[(((size_t)n * H + yy) * W + xx) * kC + cc]) : 0.f;
-        }
-        __syncthreads();
-        for (int ry = 0; ry < kTileRows; ++ry)
-            for (int px = 0; px < kTileCols; ++px) {
-                float xv[9];
-#pragma unroll
-                for (int tap = 0; tap < 9; ++tap) xv[tap] = xs[ry + tap / 3][px + tap % 3][c];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const float d = ds[ry][px][(t + 256 * m) / kC];
-#pragma unroll
-                    for (int tap = 0; tap < 9; ++tap) acc[m][tap] = fmaf(d, xv[tap], acc[m][tap]);
-                }
-                if (t < kC) accb += ds[ry][px][t];
+            for (int q = 0; q < 16; ++q) {
+                const int r = 8 * (q >> 2) + 4 * hk + (q & 3);
+                tg[nb][q] = target[(p0 + min(r, np - 1)) * kR2 + 32 * nb + i32];
             }
-    }
-    float *dst = part + (size_t)blockIdx.x * (kWl + kBl);
+        __builtin_amdgcn_wave_barrier();
+        f32x16 h[2];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const int o = (t + 256 * m) / kC;
+        for (int nb = 0; nb < 2; ++nb) {
+            const float b = bhs[nb * 32 + i32];
 #pragma unroll
-        for (int tap = 0; tap < 9; ++tap) dst[(o * kC + c) * 9 + tap] = acc[m][tap];
+            for (int q = 0; q < 16; ++q) h[nb][q] = b;
+        }
+        if constexpr (sizeof(T) == 2) {
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                const bf16x8 a = *reinterpret_cast<const bf16x8 *>(as + i32 * PS + hh * 16 + hk * 8);
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+                    h[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        a, *reinterpret_cast<const bf16x8 *>(whs + (nb * 32 + i32) * Lds<T>::wh + hh * 16 + hk * 8),
+                        h[nb], 0, 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < 16; ++s)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+                    h[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                        as[i32 * PS + 2 * s + hk], whs[(nb * 32 + i32) * Lds<T>::wh + 2 * s + hk], h[nb], 0, 0, 0);
+        }
+        // loss and g; lane: k = 32 nb + i32, register q: pixel 8 (q / 4) + 4 hk + q % 4
+        float g[2][16];
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const int r = 8 * (q >> 2) + 4 * hk + (q & 3);
+                const float d = r < np ? h[nb][q] - __int_as_float(tg[nb][q]) : 0.f;
+                loss += (double)d * d;
+                g[nb][q] = (float)(scale * d);
+                db[nb] += g[nb][q];
+                gs[r * kHtGs + 32 * nb + i32] = g[nb][q];
+            }
+        // weight gradient: rows k, columns c
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const float a = tof(as[(8 * (q >> 2) + 4 * hk + (q & 3)) * PS + i32]);
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+                dw[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(g[nb][q], a, dw[nb], 0, 0, 0);
+        }
+        __builtin_amdgcn_wave_barrier();
+        // data gradient: rows c, columns pixels
+        f32x16 dz[2] = {{}, {}};
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const float4 v = *reinterpret_cast<const float4 *>(gs + i32 * kHtGs + 32 * nb + 8 * a + 4 * hk);
+                const float gv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    dz[b & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(wt[nb][4 * a + b], gv[b], dz[b & 1], 0, 0, 0);
+            }
+        // lane: pixel i32, register q: channel 8 (q / 4) + 4 hk + q % 4
+        if (i32 < np) {
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                T o[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int c = 8 * a + 4 * hk + b;
+                    const bool on = tof(as[i32 * PS + c]) > 0.f;
+                    o[b] = fromf<T>(on ? dz[0][4 * a + b] + dz[1][4 * a + b] : 0.f);
+                }
+                T *dst = dz6 + (p0 + i32) * kC + 8 * a + 4 * hk;
+                if constexpr (sizeof(T) == 2) *reinterpret_cast<uint2 *>(dst) = *reinterpret_cast<const uint2 *>(o);
+                else *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(o);
+            }
+        }
     }
-    if (t < kC) dst[kWl + t] = accb;
+    const size_t gw = (size_t)blockIdx.x * kHtWaves + wave;
+    float *dst = part + gw * kHtPart;
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) dst[(nb * 16 + q) * 64 + lane] = dw[nb][q];
+        dst[kWh + nb * 64 + lane] = db[nb] + __shfl_xor(db[nb], 32);
+    }
+    for (int o = 32; o > 0; o >>= 1) loss += __shfl_xor(loss, o);
+    if (lane == 0) lpart[gw] = loss;
 }
 
-// Layer-0 weight-gradient partials: thread t < 288 owns (o, tap) = (t / 9, t % 9),
-// 288 <= t < 320 the bias o = t - 288.  part[w][o][tap] then part[w][288 + o].
+// Weight and bias gradient of a 32 -> 32 convolution, dw[o][c][tap] = sum_p dz[p][o]
+// x[p + tap][c], on the matrix cores with the pixels as K.  K = 32 consecutive
+// pixels of a row for BF16 (v_mfma_f32_16x16x32_bf16; 4 for FP32, 16x16x4f32), M =
+// 16 output channels, N = 16 input channels.  The operands want one channel's
+// pixels in a lane where memory has one pixel's channels together, so a lane loads
+// the channel pair (2 i, 2 i + 1) of each of its pixels straight from global memory
+// (16 lanes read a pixel's 64 bytes) and splits the pairs with byte permutes into
+// the operands of the even and of the odd channels: no LDS, no transpose.  A row of
+// x is loaded once and held as the operands of the three column taps while it
+// serves the three row taps.  The bias is one more product, against ones.
+// A wave takes 8 rows of a 32-pixel strip at a time; its 38 accumulators (152
+// registers) stay over all of a work-group's strips, and the four waves are summed
+// in LDS at the end, so a work-group writes one partial.  One wave per SIMD: the 38
+// products of a row are independent, and the next row's loads are in flight.
+// Bound by the matrix products (16 cycles each).  With one FMA per LDS operand it
+// took 1.38 ms a layer on 16 images of 250 x 274.
+constexpr int kWgRows = 8, kWgWaves = 4, kWgTiles = 38;
+constexpr int kWgPart = kWgTiles * 4 * 64;      // raw partial: every lane's accumulators
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kPastRow = 0x7ffffff0;             // an offset outside every row
+// A buffer descriptor over one row of `bytes` (none: every load returns zero).
+__device__ inline __amdgpu_buffer_rsrc_t row_rsrc(const void *row, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(row), 0, bytes, 0x00027000);
+}
+
 template <typename T>
-__global__ __launch_bounds__(320) void cnn_conv0_bwd_weight_kernel(const float *__restrict__ x0,
+__global__ __launch_bounds__(64 * kWgWaves, 1) void cnn_conv_bwd_weight_kernel(
+    const T *__restrict__ x, const T *__restrict__ dz, float *__restrict__ part, int H, int W, int B)
+{
+    __shared__ float red[2][kWgPart];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
+    f32x4 acc[kWgTiles];        // (tap, o parity, c parity), then the bias of each o parity
+#pragma unroll
+    for (int i = 0; i < kWgTiles; ++i) acc[i] = f32x4{};
+    const int strips = cdiv(W, 32), bands = cdiv(H, kWgRows * kWgWaves);
+    const long items = (long)strips * bands * B;
+    constexpr int PB = kC * (int)sizeof(T);                 // bytes per pixel
+    for (long it = blockIdx.x; it < items; it += gridDim.x) {
+        const int n = (int)(it / ((long)strips * bands)), sx = (int)(it % strips) * 32;
+        const int ya = (int)(it / strips % bands) * kWgRows * kWgWaves + wave * kWgRows;
+        const int yb = min(ya + kWgRows, H);
+        auto row_of = [&](const T *base, int y) {
+            return row_rsrc(base + ((size_t)n * H + (y >= 0 && y < H ? y : 0)) * W * kC,
+                            y >= 0 && y < H ? W * PB : 0);
+        };
+        if constexpr (sizeof(T) == 2) {
+            // pixels sx + 8 kq - 1 .. + 8 of the lane's channel pair; columns outside
+            // the row (-1 or past W) are outside the descriptor and read as zero
+            const int v0 = (sx + 8 * kq) * PB + 4 * i16;
+            const int vm = sx + 8 * kq > 0 ? v0 - PB : kPastRow;
+            unsigned rx[10], rd[8];
+            auto load_x = [&](int y) {
+                const auto r = row_of(x, y);
+                rx[0] = __builtin_amdgcn_raw_buffer_load_b32(r, vm, 0, 0);
+#pragma unroll
+                for (int j = 1; j < 10; ++j) rx[j] = __builtin_amdgcn_raw_buffer_load_b32(r, v0 + (j - 1) * PB, 0, 0);
+            };
+            auto load_d = [&](int y) {
+                const auto r = row_of(dz, y);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) rd[j] = __builtin_amdgcn_raw_buffer_load_b32(r, v0 + j * PB, 0, 0);
+            };
+            // low halves (even channels) or high halves (odd) of a run of eight
+            auto pick = [&](const unsigned *r, int parity) {
+                u32x4 o;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    o[j] = __builtin_amdgcn_perm(r[2 * j + 1], r[2 * j], parity ? 0x07060302u : 0x05040100u);
+                return __builtin_bit_cast(bf16x8, o);
+            };
+            bf16x8 xo[3][3][2];                              // [row slot][column tap][parity]
+            auto unpack_x = [&](bf16x8 (&o)[3][2]) {
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) o[dx][q] = pick(rx + dx, q);
+            };
+            const u32x4 one_bits = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+            const bf16x8 ones = __builtin_bit_cast(bf16x8, one_bits);
+            if (ya < yb) {
+                load_x(ya - 1);
+                unpack_x(xo[0]);
+                load_x(ya);
+                unpack_x(xo[1]);
+                load_x(ya + 1);
+                load_d(ya);
+            }
+#pragma unroll
+            for (int i = 0; i < kWgRows; ++i) {
+                if (ya + i < yb) {
+                    unpack_x(xo[(i + 2) % 3]);
+                    bf16x8 d[2] = {pick(rd, 0), pick(rd, 1)};
+                    load_x(ya + i + 2);
+                    load_d(ya + i + 1);
+#pragma unroll
+                    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                acc[(3 * dy + dx) * 4 + q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    d[q >> 1], xo[(i + dy) % 3][dx][q & 1], acc[(3 * dy + dx) * 4 + q], 0, 0, 0);
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        acc[36 + q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[q], ones, acc[36 + q], 0, 0, 0);
+                }
+            }
+        } else {
+            for (int y = ya; y < yb; ++y) {
+                const auto rd = row_of(dz, y);
+                const __amdgpu_buffer_rsrc_t rx[3] = {row_of(x, y - 1), row_of(x, y), row_of(x, y + 1)};
+#pragma unroll 2
+                for (int s = 0; s < 8; ++s) {
+                    const int px = sx + 4 * s + kq, v = px * PB + 8 * i16;
+                    auto load = [&](const __amdgpu_buffer_rsrc_t &r, int off) {
+                        const auto w = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+                        return make_float2(__uint_as_float(w[0]), __uint_as_float(w[1]));
+                    };
+                    const float2 d = load(rd, v);
+                    float2 xv[9];
+#pragma unroll
+                    for (int dy = 0; dy < 3; ++dy) {
+                        xv[3 * dy] = load(rx[dy], px > 0 ? v - PB : kPastRow);
+                        xv[3 * dy + 1] = load(rx[dy], v);
+                        xv[3 * dy + 2] = load(rx[dy], v + PB);
+                    }
+#pragma unroll
+                    for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            acc[tap * 4 + q] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                q >> 1 ? d.y : d.x, q & 1 ? xv[tap].y : xv[tap].x, acc[tap * 4 + q], 0, 0, 0);
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        acc[36 + q] = __builtin_amdgcn_mfma_f32_16x16x4f32(q ? d.y : d.x, 1.0f, acc[36 + q], 0, 0, 0);
+                }
+            }
+        }
+    }
+    // waves 2 and 3 into 0 and 1, then 1 into 0
+#pragma unroll
+    for (int round = 0; round < 2; ++round) {
+        const int half = 2 >> round;
+        __syncthreads();
+        if (wave >= half && wave < 2 * half) {
+#pragma unroll
+            for (int i = 0; i < kWgTiles; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) red[wave - half][(i * 4 + r) * 64 + lane] = acc[i][r];
+        }
+        __syncthreads();
+        if (wave < half) {
+#pragma unroll
+            for (int i = 0; i < kWgTiles; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][r] += red[wave][(i * 4 + r) * 64 + lane];
+        }
+    }
+    if (wave == 0) {
+        float *dst = part + (size_t)blockIdx.x * kWgPart;
+#pragma unroll
+        for (int i = 0; i < kWgTiles; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dst[(i * 4 + r) * 64 + lane] = acc[i][r];
+    }
+}
+
+// Layer-0 weight and bias gradients, dw0[o][tap] = sum_p dz[p][o] x0[p + tap], on
+// v_mfma_f32_16x16x4f32 (x0 is FP32): M = 16 output channels, N = the nine taps and,
+// as a tenth column, ones for the bias, K = 4 pixels of a row.  Each wave takes rows
+// in turn.  Bound by HBM (dz is read once).
+constexpr int kW0Part = 2 * 4 * 64;
+template <typename T>
+__global__ __launch_bounds__(256) void cnn_conv0_bwd_weight_kernel(const float *__restrict__ x0,
                                                                    const T *__restrict__ dz,
                                                                    float *__restrict__ part, int H,
                                                                    int W, int B)
 {
-    constexpr int TC = kTileCols + 2;
-    __shared__ float xs[kTileRows + 2][TC];
-    __shared__ float ds[kTileRows][kTileCols][kC + 1];
-    const int t = threadIdx.x;
-    const int tx = cdiv(W, kTileCols), ty = cdiv(H, kTileRows);
-    const long ntiles = (long)tx * ty * B;
-    const int o = t < kW0 ? t / 9 : t - kW0, tap = t < kW0 ? t % 9 : 4;
-    const int dy = tap / 3, dx = tap % 3;
-    float acc = 0.f;
-    for (long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int n = tile / ((long)tx * ty), y0 = (tile / tx) % ty * kTileRows,
-                  x0c = tile % tx * kTileCols;
-        __syncthreads();
-        for (int e = t; e < (kTileRows + 2) * TC; e += blockDim.x) {
-            const int px = e % TC, ry = e / TC;
-            const int yy = y0 + ry - 1, xx = x0c + px - 1;
-            xs[ry][px] = (yy >= 0 && yy < H && xx >= 0 && xx < W) ? x0[((size_t)n * H + yy) * W + xx] : 0.f;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
+    const int dy = i16 < 9 ? i16 / 3 - 1 : 0, dx = i16 < 9 ? i16 % 3 - 1 : 0;
+    constexpr int PB = kC * (int)sizeof(T);
+    f32x4 acc[2] = {{}, {}};
+    const long gw = (long)blockIdx.x * 4 + wave, rows = (long)H * B;
+    for (long row = gw; row < rows; row += (long)gridDim.x * 4) {
+        const int y = (int)(row % H), yy = y + dy;
+        const auto rd = row_rsrc(dz + (size_t)row * W * kC, W * PB);
+        const bool yok = i16 < 9 && yy >= 0 && yy < H;
+        const float *xr = x0 + (size_t)(row - y + (yok ? yy : y)) * W;
+        for (int s0 = 0; s0 < W; s0 += 32)
+#pragma unroll
+        for (int s = s0; s < s0 + 32; s += 4) {     // past W dz reads as zero
+            const int px = s + kq, xx = px + dx;
+            const float xl = xr[min(max(xx, 0), W - 1)];
+            const float b = i16 == 9 ? 1.f : (yok && xx >= 0 && xx < W ? xl : 0.f);
+            float2 d;
+            if constexpr (sizeof(T) == 2) {
+                const unsigned w = __builtin_amdgcn_raw_buffer_load_b32(rd, px * PB + 4 * i16, 0, 0);
+                d = make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
+            } else {
+                const auto w = __builtin_amdgcn_raw_buffer_load_b64(rd, px * PB + 8 * i16, 0, 0);
+                d = make_float2(__uint_as_float(w[0]), __uint_as_float(w[1]));
+            }
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.x, b, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.y, b, acc[1], 0, 0, 0);
         }
-        for (int e = t; e < kTileRows * kTileCols * kC; e += blockDim.x) {
-            const int cc = e % kC, px = (e / kC) % kTileCols, ry = e / (kC * kTileCols);
-            const int yy = y0 + ry, xx = x0c + px;
-            ds[ry][px][cc] = (yy < H && xx < W) ? tof(dz[(((size_t)n * H + yy) * W + xx) * kC + cc]) : 0.f;
-        }
-        __syncthreads();
-        for (int ry = 0; ry < kTileRows; ++ry)
-            for (int px = 0; px < kTileCols; ++px)
-                acc = t < kW0 ? fmaf(ds[ry][px][o], xs[ry + dy][px + dx], acc) : acc + ds[ry][px][o];
     }
-    part[(size_t)blockIdx.x * (kW0 + kB0) + t] = acc;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[(size_t)gw * kW0Part + (q * 4 + r) * 64 + lane] = acc[q][r];
 }
 
-// grad[off + e] = sum over the partials q of part[q][e] (FP64, fixed order)
-__global__ void cnn_reduce_kernel(const float *__restrict__ part, int nparts, int width,
-                                  float *__restrict__ grad, int off)
+// grad[off + where(e)] = sum over the partials q of part[q][e] (FP64, fixed order:
+// 16 interleaved sums, added in turn).  e counts a kernel's accumulators as its lanes
+// hold them; KIND says which gradient they are.
+enum ReduceKind { kReduceConv, kReduceHead, kReduceConv0 };
+template <int KIND>
+__global__ __launch_bounds__(1024) void cnn_reduce_kernel(const float *__restrict__ part, int nparts,
+                                                          int width, float *__restrict__ grad)
 {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= width) return;
+    __shared__ double red[16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int e = blockIdx.x * 64 + lane;                    // width is a multiple of 64
     double s = 0.0;
-    for (int q = 0; q < nparts; ++q) s += part[(size_t)q * width + e];
-    grad[off + e] = (float)s;
+#pragma unroll 4
+    for (int q = wave; q < nparts; q += 16) s += part[(size_t)q * width + e];
+    red[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int w = 1; w < 16; ++w) s += red[w][lane];
+    const int reg = blockIdx.x, i16 = lane & 15, m = 4 * (lane >> 4) + (reg & 3);
+    if constexpr (KIND == kReduceConv) {
+        const int tile = reg >> 2;
+        if (tile < 36) {
+            const int o = 2 * m + ((tile >> 1) & 1), c = 2 * i16 + (tile & 1);
+            grad[(o * kC + c) * 9 + (tile >> 2)] = (float)s;
+        } else if (i16 == 0) {
+            grad[kWl + 2 * m + (tile - 36)] = (float)s;
+        }
+    } else if constexpr (KIND == kReduceHead) {
+        const int i32 = lane & 31, hk = lane >> 5;
+        if (reg < 32) {
+            const int q = reg & 15, k = 32 * (reg >> 4) + 8 * (q >> 2) + 4 * hk + (q & 3);
+            grad[k * kC + i32] = (float)s;
+        } else if (hk == 0) {
+            grad[kWh + 32 * (reg - 32) + i32] = (float)s;
+        }
+    } else {
+        const int o = 2 * m + (reg >> 2);
+        if (i16 < 9) grad[o * 9 + i16] = (float)s;
+        else if (i16 == 9) grad[kW0 + o] = (float)s;
+    }
 }
 
 __global__ void cnn_adam_kernel(float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
@@ -1233,10 +1448,13 @@ static size_t a256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Workspace regions for a batch of B images of H x W pixels.
 struct CnnLayout {
-    size_t x0, act[kL], dz[2], logits, target, glog, wm, wt, part, lpart, grad, total;
+    size_t x0, act[kL], dz[2], logits, target, wm, wt, part, lpart, grad, total;
     int n_act;
 };
-constexpr int kLossParts = 1024;
+constexpr int kHeadGroups = 512;    // work-groups of the head's training pass (two per CU)
+constexpr int kConv0Groups = 512;
+constexpr size_t kPartFloats = std::max({(size_t)kMaxPartials * kWgPart, (size_t)kHeadGroups * kHtWaves * kHtPart,
+                                         (size_t)kConv0Groups * 4 * kW0Part});
 
 static CnnLayout cnn_layout(int B, int H, int W, bool fp32, bool train) {
     const size_t npx = (size_t)B * H * W, es = fp32 ? 4 : 2;
@@ -1248,14 +1466,13 @@ static CnnLayout cnn_layout(int B, int H, int W, bool fp32, bool train) {
     for (int l = 0; l < L.n_act; ++l) L.act[l] = take(es * npx * kC);
     L.wm = take(es * (kL - 1) * kWl);
     L.wt = take(es * (kL - 1) * kWl);
-    L.logits = take(sizeof(float) * npx * kR2);
+    if (!train) L.logits = take(sizeof(float) * npx * kR2);
     if (train) {
         L.dz[0] = take(es * npx * kC);
         L.dz[1] = take(es * npx * kC);
         L.target = take(sizeof(float) * npx * kR2);
-        L.glog = take(sizeof(float) * npx * kR2);
-        L.part = take(sizeof(float) * kMaxPartials * (kWl + kBl));
-        L.lpart = take(sizeof(double) * kLossParts);
+        L.part = take(sizeof(float) * kPartFloats);
+        L.lpart = take(sizeof(double) * kHeadGroups * kHtWaves);
         L.grad = take(sizeof(float) * kParams);
     }
     L.total = o;
@@ -1365,7 +1582,6 @@ static hipError_t gradients_t(const float *params, const float *x0, const float 
     T *act[kL];
     for (int l = 0; l < kL; ++l) act[l] = (T *)(ws + L.act[l]);
     T *dz[2] = {(T *)(ws + L.dz[0]), (T *)(ws + L.dz[1])};
-    float *logits = (float *)(ws + L.logits), *glog = (float *)(ws + L.glog);
     int *target = (int *)(ws + L.target);
     float *part = (float *)(ws + L.part);
     double *lpart = (double *)(ws + L.lpart);
@@ -1374,45 +1590,38 @@ static hipError_t gradients_t(const float *params, const float *x0, const float 
     hipError_t e = run_forward<T>(params, x0, act, kL, (T *)(ws + L.wm), (T *)(ws + L.wt), B, H, W,
                                   st, &last);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(cnn_head_kernel<T>, dim3((unsigned)cdiv(npx, (size_t)128)), dim3(256), 0, st,
-                       act[kL - 1], params, logits, npx);
-    // target and loss
+    // target, then the whole head
     hipLaunchKernelGGL(cnn_fill_kernel, dim3(1024), dim3(256), 0, st, target, count, 0);
     if (n_mb > 0)
         hipLaunchKernelGGL(cnn_target_kernel, dim3(n_mb), dim3(128), 0, st, (const float2 *)mb_zu,
                            mb_img, n_mb, B, target, H, W);
-    hipLaunchKernelGGL(cnn_loss_kernel, dim3(kLossParts), dim3(256), 0, st, logits, target, glog,
-                       count, lpart);
-    hipLaunchKernelGGL(cnn_loss_final_kernel, dim3(1), dim3(64), 0, st, lpart, kLossParts,
+    const int gh = (int)std::min((size_t)kHeadGroups, cdiv(npx, (size_t)32 * kHtWaves));
+    hipLaunchKernelGGL(cnn_head_train_kernel<T>, dim3(gh), dim3(64 * kHtWaves), 0, st, act[kL - 1], params,
+                       target, dz[0], part, lpart, npx);
+    hipLaunchKernelGGL(cnn_loss_final_kernel, dim3(1), dim3(64), 0, st, lpart, gh * kHtWaves,
                        1.0 / (double)count, loss);
-    // head
-    const int gh = (int)std::min((size_t)kMaxPartials, cdiv(npx, (size_t)kHeadPx));
-    hipLaunchKernelGGL(cnn_head_bwd_weight_kernel<T>, dim3(gh), dim3(256), 0, st, glog, act[kL - 1],
-                       part, npx);
-    hipLaunchKernelGGL(cnn_reduce_kernel, dim3(cdiv(kWh + kBh, 256)), dim3(256), 0, st, part, gh,
-                       kWh + kBh, grad, off_wh());
-    hipLaunchKernelGGL(cnn_head_bwd_data_kernel<T>, dim3((unsigned)cdiv(npx, (size_t)256)), dim3(256),
-                       0, st, glog, params, act[kL - 1], dz[0], npx);
+    hipLaunchKernelGGL(cnn_reduce_kernel<kReduceHead>, dim3(kHtPart / 64), dim3(1024), 0, st, part,
+                       gh * kHtWaves, kHtPart, grad + off_wh());
     // conv layers 5..1: weight gradient, then the data gradient through the mask below
-    const dim3 grid(cdiv(W, kTileCols), cdiv(H, kTileRows), B);
-    const long ntiles = (long)grid.x * grid.y * grid.z;
-    const int gw = (int)std::min((long)kMaxPartials, ntiles);
+    const long items = (long)cdiv(W, 32) * cdiv(H, kWgRows * kWgWaves) * B;
+    const int gw = (int)std::min((long)kMaxPartials, items);
     const T *wt = (const T *)(ws + L.wt);
     int cur = 0;
     for (int l = kL - 1; l >= 1; --l) {
-        hipLaunchKernelGGL(cnn_conv_bwd_weight_kernel<T>, dim3(gw), dim3(256), 0, st, act[l - 1],
+        hipLaunchKernelGGL(cnn_conv_bwd_weight_kernel<T>, dim3(gw), dim3(64 * kWgWaves), 0, st, act[l - 1],
                            dz[cur], part, H, W, B);
-        hipLaunchKernelGGL(cnn_reduce_kernel, dim3(cdiv(kWl + kBl, 256)), dim3(256), 0, st, part, gw,
-                           kWl + kBl, grad, off_w(l));
+        hipLaunchKernelGGL(cnn_reduce_kernel<kReduceConv>, dim3(kWgPart / 64), dim3(1024), 0, st, part, gw,
+                           kWgPart, grad + off_w(l));
         hipLaunchKernelGGL((cnn_conv_kernel<T, true>), dim3(conv_grid(B, H, W)), dim3(256), 0, st,
                            dz[cur], wt + (size_t)(l - 1) * kWl, (const float *)nullptr,
                            act[l - 1], dz[cur ^ 1], H, W, B);
         cur ^= 1;
     }
-    hipLaunchKernelGGL(cnn_conv0_bwd_weight_kernel<T>, dim3(gw), dim3(kW0 + kB0), 0, st, x0, dz[cur],
-                       part, H, W, B);
-    hipLaunchKernelGGL(cnn_reduce_kernel, dim3(cdiv(kW0 + kB0, 256)), dim3(256), 0, st, part, gw,
-                       kW0 + kB0, grad, 0);
+    const int g0 = (int)std::min((long)kConv0Groups, cdiv((long)H * B, 4L));
+    hipLaunchKernelGGL(cnn_conv0_bwd_weight_kernel<T>, dim3(g0), dim3(256), 0, st, x0, dz[cur], part, H,
+                       W, B);
+    hipLaunchKernelGGL(cnn_reduce_kernel<kReduceConv0>, dim3(kW0Part / 64), dim3(1024), 0, st, part, g0 * 4,
+                       kW0Part, grad);
     return hipGetLastError();
 }
 
