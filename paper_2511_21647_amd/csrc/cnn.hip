@@ -1040,21 +1040,19 @@ __global__ __launch_bounds__(64 * kHtWaves, 2) void cnn_head_train_kernel(
     constexpr int PS = Lds<T>::px;
     __shared__ __attribute__((aligned(16))) T whs[kR2 * Lds<T>::wh];
     __shared__ float bhs[kR2];
+    __shared__ float wf[kWh];
     __shared__ __attribute__((aligned(16))) T as_all[kHtWaves][32 * PS];
     __shared__ __attribute__((aligned(16))) float gs_all[kHtWaves][32 * kHtGs];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i32 = lane & 31, hk = lane >> 5;
     stage_head<T>(p, whs, bhs);
+    // the weights of the data gradient stay in FP32: its A operand is wh[k][c = lane]
+    for (int e = threadIdx.x; e < kWh; e += 64 * kHtWaves) wf[e] = p[off_wh() + e];
     __syncthreads();
     T *as = as_all[wave];
     float *gs = gs_all[wave];
+    // 2 / count as the sum of two floats: the product with d rounds once
     const double scale = 2.0 / (double)(npx * kR2);
-    // A operand of the data gradient: wh[k][c = lane], k = 32 nb + 8 a + 4 hk + b
-    float wt[2][16];
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int q = 0; q < 16; ++q)
-            wt[nb][q] = p[off_wh() + (32 * nb + 8 * (q >> 2) + 4 * hk + (q & 3)) * kC + i32];
+    const float s_hi = (float)scale, s_lo = (float)(scale - (double)s_hi);
     f32x16 dw[2] = {{}, {}};
     float db[2] = {0.f, 0.f};
     double loss = 0.0;
@@ -1117,7 +1115,7 @@ __global__ __launch_bounds__(64 * kHtWaves, 2) void cnn_head_train_kernel(
                 const int r = 8 * (q >> 2) + 4 * hk + (q & 3);
                 const float d = r < np ? h[nb][q] - __int_as_float(tg[nb][q]) : 0.f;
                 loss += (double)d * d;
-                g[nb][q] = (float)(scale * d);
+                g[nb][q] = fmaf(d, s_hi, d * s_lo);
                 db[nb] += g[nb][q];
                 gs[r * kHtGs + 32 * nb + i32] = g[nb][q];
             }
@@ -1140,7 +1138,8 @@ __global__ __launch_bounds__(64 * kHtWaves, 2) void cnn_head_train_kernel(
                 const float gv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                 for (int b = 0; b < 4; ++b)
-                    dz[b & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(wt[nb][4 * a + b], gv[b], dz[b & 1], 0, 0, 0);
+                    dz[b & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                        wf[(32 * nb + 8 * a + 4 * hk + b) * kC + i32], gv[b], dz[b & 1], 0, 0, 0);
             }
         // lane: pixel i32, register q: channel 8 (q / 4) + 4 hk + q % 4
         if (i32 < np) {
@@ -1204,7 +1203,8 @@ __global__ __launch_bounds__(64 * kWgWaves, 1) void cnn_conv_bwd_weight_kernel(
     const T *__restrict__ x, const T *__restrict__ dz, float *__restrict__ part, int H, int W, int B)
 {
     __shared__ float red[2][kWgPart];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
+    const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // rows are uniform in a wave
     f32x4 acc[kWgTiles];        // (tap, o parity, c parity), then the bias of each o parity
 #pragma unroll
     for (int i = 0; i < kWgTiles; ++i) acc[i] = f32x4{};
@@ -1224,14 +1224,15 @@ __global__ __launch_bounds__(64 * kWgWaves, 1) void cnn_conv_bwd_weight_kernel(
             // the row (-1 or past W) are outside the descriptor and read as zero
             const int v0 = (sx + 8 * kq) * PB + 4 * i16;
             const int vm = sx + 8 * kq > 0 ? v0 - PB : kPastRow;
-            unsigned rx[10], rd[8];
-            auto load_x = [&](int y) {
+            // rows in flight: two ahead (a row's products take less than the latency)
+            unsigned rxs[2][10], rds[2][8];
+            auto load_x = [&](int y, unsigned (&rx)[10]) {
                 const auto r = row_of(x, y);
                 rx[0] = __builtin_amdgcn_raw_buffer_load_b32(r, vm, 0, 0);
 #pragma unroll
                 for (int j = 1; j < 10; ++j) rx[j] = __builtin_amdgcn_raw_buffer_load_b32(r, v0 + (j - 1) * PB, 0, 0);
             };
-            auto load_d = [&](int y) {
+            auto load_d = [&](int y, unsigned (&rd)[8]) {
                 const auto r = row_of(dz, y);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) rd[j] = __builtin_amdgcn_raw_buffer_load_b32(r, v0 + j * PB, 0, 0);
@@ -1245,7 +1246,7 @@ __global__ __launch_bounds__(64 * kWgWaves, 1) void cnn_conv_bwd_weight_kernel(
                 return __builtin_bit_cast(bf16x8, o);
             };
             bf16x8 xo[3][3][2];                              // [row slot][column tap][parity]
-            auto unpack_x = [&](bf16x8 (&o)[3][2]) {
+            auto unpack_x = [&](const unsigned (&rx)[10], bf16x8 (&o)[3][2]) {
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
@@ -1254,20 +1255,25 @@ __global__ __launch_bounds__(64 * kWgWaves, 1) void cnn_conv_bwd_weight_kernel(
             const u32x4 one_bits = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
             const bf16x8 ones = __builtin_bit_cast(bf16x8, one_bits);
             if (ya < yb) {
-                load_x(ya - 1);
-                unpack_x(xo[0]);
-                load_x(ya);
-                unpack_x(xo[1]);
-                load_x(ya + 1);
-                load_d(ya);
+                unsigned first[2][10];
+                load_x(ya - 1, first[0]);
+                load_x(ya, first[1]);
+                load_x(ya + 1, rxs[0]);
+                load_d(ya, rds[0]);
+                load_x(ya + 2, rxs[1]);
+                load_d(ya + 1, rds[1]);
+                unpack_x(first[0], xo[0]);
+                unpack_x(first[1], xo[1]);
             }
 #pragma unroll
             for (int i = 0; i < kWgRows; ++i) {
                 if (ya + i < yb) {
-                    unpack_x(xo[(i + 2) % 3]);
-                    bf16x8 d[2] = {pick(rd, 0), pick(rd, 1)};
-                    load_x(ya + i + 2);
-                    load_d(ya + i + 1);
+                    unpack_x(rxs[i & 1], xo[(i + 2) % 3]);
+                    bf16x8 d[2] = {pick(rds[i & 1], 0), pick(rds[i & 1], 1)};
+                    if (i + 2 < kWgRows) {
+                        load_x(ya + i + 3, rxs[i & 1]);
+                        load_d(ya + i + 2, rds[i & 1]);
+                    }
 #pragma unroll
                     for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
@@ -1352,7 +1358,8 @@ __global__ __launch_bounds__(256) void cnn_conv0_bwd_weight_kernel(const float *
                                                                    float *__restrict__ part, int H,
                                                                    int W, int B)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
+    const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // rows are uniform in a wave
     const int dy = i16 < 9 ? i16 / 3 - 1 : 0, dx = i16 < 9 ? i16 % 3 - 1 : 0;
     constexpr int PB = kC * (int)sizeof(T);
     f32x4 acc[2] = {{}, {}};
@@ -1380,10 +1387,14 @@ __global__ __launch_bounds__(256) void cnn_conv0_bwd_weight_kernel(const float *
             acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.y, b, acc[1], 0, 0, 0);
         }
     }
+    __shared__ float red[4][kW0Part];
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) part[(size_t)gw * kW0Part + (q * 4 + r) * 64 + lane] = acc[q][r];
+        for (int r = 0; r < 4; ++r) red[wave][(q * 4 + r) * 64 + lane] = acc[q][r];
+    __syncthreads();
+    for (int e = threadIdx.x; e < kW0Part; e += 256)
+        part[(size_t)blockIdx.x * kW0Part + e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
 }
 
 // grad[off + where(e)] = sum over the partials q of part[q][e] (FP64, fixed order:
@@ -1452,9 +1463,9 @@ struct CnnLayout {
     int n_act;
 };
 constexpr int kHeadGroups = 512;    // work-groups of the head's training pass (two per CU)
-constexpr int kConv0Groups = 512;
+constexpr int kConv0Groups = 1024;
 constexpr size_t kPartFloats = std::max({(size_t)kMaxPartials * kWgPart, (size_t)kHeadGroups * kHtWaves * kHtPart,
-                                         (size_t)kConv0Groups * 4 * kW0Part});
+                                         (size_t)kConv0Groups * kW0Part});
 
 static CnnLayout cnn_layout(int B, int H, int W, bool fp32, bool train) {
     const size_t npx = (size_t)B * H * W, es = fp32 ? 4 : 2;
@@ -1620,7 +1631,7 @@ static hipError_t gradients_t(const float *params, const float *x0, const float 
     const int g0 = (int)std::min((long)kConv0Groups, cdiv((long)H * B, 4L));
     hipLaunchKernelGGL(cnn_conv0_bwd_weight_kernel<T>, dim3(g0), dim3(256), 0, st, x0, dz[cur], part, H,
                        W, B);
-    hipLaunchKernelGGL(cnn_reduce_kernel<kReduceConv0>, dim3(kW0Part / 64), dim3(1024), 0, st, part, g0 * 4,
+    hipLaunchKernelGGL(cnn_reduce_kernel<kReduceConv0>, dim3(kW0Part / 64), dim3(1024), 0, st, part, g0,
                        kW0Part, grad);
     return hipGetLastError();
 }
