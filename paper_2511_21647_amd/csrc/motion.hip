@@ -23,6 +23,7 @@
 //                     3-point sub-pixel fit per axis
 //   mot_mean_kernel   per-orientation means and the 3D motion per frame
 #include "common.h"
+#include "roots.h"
 
 #include <math.h>
 
@@ -32,7 +33,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kMotFrames = 32;     // frames per work-group: the MFMA's M
 constexpr int kMotRows = 16;       // slice rows per work-group
-constexpr int kMotStage = 256;     // pixels staged in LDS per step
+constexpr int kMotStage = 128;     // pixels staged in LDS per step
+constexpr int kMotFly = kMotFrames * kMotStage / 256;   // of those, values per thread
 constexpr int kMotAS = kMotStage + 1;
 constexpr int kMotMaxLag = 10;     // lag window |dz|, |du| <= L, L <= 10
 
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(1024) void mot_ref_kernel(const float2 *__restrict_
 }
 
 // LDS: the reference band with a circular halo of L rows and columns, then the
-// staged envelopes [32 frames][256 pixels (+1)]; reused for the wave reduction.
+// staged envelopes [32 frames][128 pixels (+1)]; reused for the wave reduction.
 size_t mot_corr_lds(int nu, int L, int NT) {
     const size_t tiles = (size_t)(kMotRows + 2 * L) * (nu + 2 * L) + (size_t)kMotFrames * kMotAS;
     const size_t red = (size_t)NT * 32 * 32;
@@ -91,7 +93,7 @@ size_t mot_corr_lds(int nu, int L, int NT) {
 }
 
 template <int NT>
-__global__ __launch_bounds__(256) void mot_corr_kernel(const float2 *__restrict__ S,
+__global__ __launch_bounds__(256, NT <= 10 ? 3 : 2) void mot_corr_kernel(const float2 *__restrict__ S,
                                                        const float *__restrict__ bref, MotArgs a,
                                                        float *__restrict__ part,
                                                        double *__restrict__ astat)
@@ -138,63 +140,83 @@ __global__ __launch_bounds__(256) void mot_corr_kernel(const float2 *__restrict_
 
     const int npx = rows * a.nu;
     const int f0 = fb * kMotFrames;
-    const float2 *Sb = S + (size_t)s * a.F * a.npix + (size_t)z0 * a.nu;
-    // the next step's 32 frames of this thread's pixel, in flight during the MFMAs
-    float2 xa[kMotFrames];
+    // the frames' values through a buffer descriptor on frame f0 from the band's first
+    // row on: a frame's scalar offset plus the pixel's, zeros past the last frame and,
+    // by an offset outside it, past the band's pixels
+    const int frame_bytes = a.npix * (int)sizeof(float2);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(S + ((size_t)s * a.F + f0) * a.npix + (size_t)z0 * a.nu), 0,
+        min(a.F - f0, kMotFrames) * frame_bytes - z0 * a.nu * (int)sizeof(float2), 0x00027000);
+    // the next step's values of this thread (one pixel, half of the frames), in flight
+    // during the MFMAs
+    const int tp = t % kMotStage, tf = __builtin_amdgcn_readfirstlane(t / kMotStage) * kMotFly;
+    float2 xa[kMotFly];
     auto fetch = [&](int p0n) {
-        const int p = p0n + t;
+        const int p = p0n + tp, off = p < npx ? p * (int)sizeof(float2) : 0x7ffffff0;
 #pragma unroll
-        for (int fl = 0; fl < kMotFrames; ++fl) {
-            const int f = f0 + fl;
-            xa[fl] = (f < a.F && p < npx) ? Sb[(size_t)f * a.npix + p] : make_float2(0.f, 0.f);
+        for (int i = 0; i < kMotFly; ++i) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, off, (tf + i) * frame_bytes, 0);
+            xa[i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
         }
     };
     fetch(0);
     for (int p0 = 0; p0 < npx; p0 += kMotStage) {
         __syncthreads();                                // Bs written / previous As consumed
 #pragma unroll
-        for (int fl = 0; fl < kMotFrames; ++fl)
-            As[fl * kMotAS + t] = sqrtf(xa[fl].x * xa[fl].x + xa[fl].y * xa[fl].y);
+        for (int f8 = 0; f8 < kMotFly; f8 += 8) {
+            float m2[8], r[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) m2[i] = xa[f8 + i].x * xa[f8 + i].x + xa[f8 + i].y * xa[f8 + i].y;
+            exact_roots<8>(m2, r);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) As[(tf + f8 + i) * kMotAS + tp] = r[i];
+        }
         __syncthreads();
         if (p0 + kMotStage < npx) fetch(p0 + kMotStage);
-        {   // sums of a and a^2 per frame: 8 threads per frame, 32 pixels each
-            const int fl = t >> 3, q = t & 7;
-            float s1 = 0.f, s2 = 0.f;
-            for (int i = 0; i < 32; ++i) {
-                const float v = As[fl * kMotAS + q * 32 + i];
-                s1 += v;
-                s2 = fmaf(v, v, s2);
-            }
-            for (int o = 1; o < 8; o <<= 1) {
-                s1 += __shfl_xor(s1, o);
-                s2 += __shfl_xor(s2, o);
-            }
-            d1 += s1;
-            d2 += s2;
-        }
-        // pixels p0 + 128 ph .. p0 + 128 ph + 127, two per MFMA; (pz, pu) of this
+        // sums of a and a^2 of this lane's frame over the 32 pixels it feeds to the
+        // matrix products (FP32 within the step, FP64 across steps)
+        float s1 = 0.f, s2 = 0.f;
+        // pixels p0 + 64 ph .. p0 + 64 ph + 63, two per MFMA; (pz, pu) of this
         // lane's pixel advance by two per step (pixels past the band read an
         // in-band reference value and contribute a = 0)
-        int pz = (p0 + ph * 128 + hk) / a.nu, pu = (p0 + ph * 128 + hk) - pz * a.nu;
-#pragma unroll 2
-        for (int st = 0; st < 64; ++st) {
-            const int pl = ph * 128 + 2 * st + hk;
-            const float av = As[i32 * kMotAS + pl];
+        constexpr int kHalf = kMotStage / 2;
+        int pz = (p0 + ph * kHalf + hk) / a.nu, pu = (p0 + ph * kHalf + hk) - pz * a.nu;
+        // the operands of step st: this lane's frame and pixel, and the reference at the
+        // pixel less each lag (a tile slot past the last, odd NT only, reads the lag-0
+        // value and is never stored)
+        auto operands = [&](int st, float &av, float (&bv)[NH]) {
+            av = As[i32 * kMotAS + ph * kHalf + 2 * st + hk];
             const int base = (min(pz, rows - 1) + L) * W2 + pu + L;
-            // every tile slot runs (a slot past the last tile, odd NT only, reads
-            // the lag-0 value and is never stored), so the NH reads issue
-            // back to back ahead of their MFMAs
-            float bv[NH];
 #pragma unroll
             for (int tt = 0; tt < NH; ++tt) bv[tt] = Bs[base - off[tt]];
-#pragma unroll
-            for (int tt = 0; tt < NH; ++tt)
-                acc[tt] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv[tt], acc[tt], 0, 0, 0);
             pu += 2;
             const bool wrap = pu >= a.nu;
             pu -= wrap ? a.nu : 0;
             pz += wrap ? 1 : 0;
+        };
+        auto products = [&](float av, const float (&bv)[NH]) {
+            s1 += av;
+            s2 = fmaf(av, av, s2);
+#pragma unroll
+            for (int tt = 0; tt < NH; ++tt)
+                acc[tt] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv[tt], acc[tt], 0, 0, 0);
+        };
+        // the next step's operands are read during this step's products (left to itself
+        // the compiler reads each just before its product and waits)
+        float av0, av1, bv0[NH], bv1[NH];
+        operands(0, av0, bv0);
+        for (int st = 0; st < kHalf / 2; st += 2) {
+            operands(st + 1, av1, bv1);
+            __builtin_amdgcn_sched_barrier(0);
+            products(av0, bv0);
+            __builtin_amdgcn_sched_barrier(0);
+            operands(min(st + 2, kHalf / 2 - 1), av0, bv0);
+            __builtin_amdgcn_sched_barrier(0);
+            products(av1, bv1);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        d1 += s1;
+        d2 += s2;
     }
     // sum the two waves of each tile half in a fixed order, in LDS
     float *Red = smem;                                  // [NT][32 frames][32 lags]
@@ -221,10 +243,19 @@ __global__ __launch_bounds__(256) void mot_corr_kernel(const float2 *__restrict_
         const int r = e / (NT * 32), j = e % (NT * 32);
         dst[e] = Red[((j >> 5) * 32 + r) * 32 + (j & 31)];
     }
-    if ((t & 7) == 0) {
-        double *ds = astat + (blk * kMotFrames + (t >> 3)) * 2;
-        ds[0] = d1;
-        ds[1] = d2;
+    // the frame's four pixel sets (half ph, parity hk), in a fixed order
+    __syncthreads();
+    double *ds4 = reinterpret_cast<double *>(smem);     // [ph][hk][2][32]
+    if (th == 0) {
+        ds4[((ph * 2 + hk) * 2) * 32 + i32] = d1;
+        ds4[((ph * 2 + hk) * 2 + 1) * 32 + i32] = d2;
+    }
+    __syncthreads();
+    if (t < 2 * kMotFrames) {
+        const int c = t >> 5;
+        double v = 0.0;
+        for (int q = 0; q < 4; ++q) v += ds4[(q * 2 + c) * 32 + i32];
+        astat[(blk * kMotFrames + i32) * 2 + c] = v;
     }
 }
 

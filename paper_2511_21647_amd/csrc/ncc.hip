@@ -17,6 +17,7 @@
 // Output order is (plane, frame, row, column) without any sort: bands are full
 // width and are laid out in that order.
 #include "common.h"
+#include "roots.h"
 
 #include <float.h>
 #include <math.h>
@@ -75,30 +76,6 @@ __device__ inline float subpix(float nm, float n0, float np) {
 // and the NCC windows see the same value.
 __device__ inline float ncc_mag2(float2 v) { return fmaf(v.x, v.x, v.y * v.y); }
 __device__ inline float ncc_mag(float2 v) { return sqrtf(ncc_mag2(v)); }
-
-// Square roots of N values at once, correctly rounded as sqrtf's: the hardware
-// reciprocal root and one Newton step on the root's residual, which an exhaustive
-// comparison over every float from 2^-96 up finds equal to sqrtf.  Smaller values
-// (zeros among them), infinities and NaN take sqrtf itself, the whole wave's N at
-// once.  6 instructions a value instead of sqrtf's 16.
-template <int N>
-__device__ inline void ncc_roots(const float (&x)[N], float (&r)[N]) {
-    float lo = x[0], hi = x[0];
-    bool nan = false;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const float y = __builtin_amdgcn_rsqf(x[i]);
-        const float s = x[i] * y;
-        r[i] = fmaf(fmaf(-s, s, x[i]), 0.5f * y, s);
-        lo = fminf(lo, x[i]);
-        hi = fmaxf(hi, x[i]);
-        nan |= x[i] != x[i];
-    }
-    if (__ballot(!(lo >= 0x1p-96f && hi < INFINITY) || nan)) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) r[i] = sqrtf(x[i]);
-    }
-}
 
 // A regional maximum as ncc_stream_kernel stages it (the size of a record): the
 // NCC there and at the four neighbours that the sub-pixel fit reads.
@@ -196,7 +173,7 @@ __global__ __launch_bounds__(kNccMaxThreads, H <= 4 ? 5 : 4) void ncc_stream_ker
         float x[N], r[N];
 #pragma unroll
         for (int i = 0; i < N; ++i) x[i] = ncc_mag2(raw[i]);
-        ncc_roots<N>(x, r);
+        exact_roots<N>(x, r);
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const unsigned zmask = (unsigned)(z + i) < (unsigned)nz ? ~0u : 0u;     // uniform
