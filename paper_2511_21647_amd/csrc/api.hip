@@ -172,8 +172,7 @@ static void layout_workspace(ulm_ctx *ctx) {
     w.tscratch = take(sizeof(double) * planes * cc * 6 * F);
     w.xscratch = take(sizeof(double2) * planes * cc * F);
     w.hvec = take(sizeof(double2) * planes * F * F);
-    w.vbuf = take(sizeof(double2) * planes * 2 * F);
-    w.pbuf = take(sizeof(double2) * planes * 2 * F);
+    w.xbuf = take(sizeof(double2) * planes * 6 * F);
     w.bar = take(sizeof(int) * planes * kBarStride);
     w.eflag = take(sizeof(int) * planes);
     w.fmax = take(sizeof(float) * planes * F);

@@ -128,7 +128,7 @@ struct Workspace {
     size_t tscratch;    // [planes][c][6][F] f64    inverse-iteration scratch
     size_t xscratch;    // [planes][c][F] c128      back-transformed vectors
     size_t hvec;        // [planes][F][F] c128      Householder vectors
-    size_t vbuf, pbuf;  // [planes][2][F] c128      column / p exchange (by step parity)
+    size_t xbuf;        // [planes][2][3][F] c128   p and column exchange (by step modulo 3)
     size_t bar;         // [planes][kBarStride] i32 grid-barrier flags + XCC mask
     size_t eflag;       // [planes] i32
     size_t fmax;        // [planes][F] f32

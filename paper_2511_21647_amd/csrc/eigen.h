@@ -1,5 +1,5 @@
-// Arguments of the cooperative FP64 Hermitian eigensolver (eigen.hip), shared
-// by the clutter filter's driver (svd.hip).
+// Arguments of the cooperative FP64 Hermitian eigensolvers (eigen.hip; eigen_lds.hip
+// for the split-precision form), shared by the clutter filter's driver (svd.hip).
 #pragma once
 
 #include "common.h"
@@ -19,8 +19,8 @@ struct EigArgs {
     double2 *V;         // [planes][F][c] clutter eigenvectors
     double *tscr;       // [planes][c][6][F]
     double2 *xscr;      // [planes][c][F]
-    double2 *vbuf;      // [planes][2][F] published columns (double-buffered by step parity)
-    double2 *pbuf;      // [planes][2][F] published p = tau A v
+    double2 *xbuf;      // [planes][2][3][F] published p = tau A v, then columns, by step modulo 3
+                        // (eigen_lds.hip: by step modulo 2, in the first four)
     int *bar;           // [planes][kBarStride] barrier flags and the XCC mask, zero at launch
     int *flag;          // [planes] non-finite input
     int *status;
@@ -30,8 +30,13 @@ struct EigArgs {
     int plane0;
 };
 
-int eigen_coop_width(int F);
+int eigen_coop_width(int F, int planes);
 size_t eigen_coop_lds(int F, int c);
 hipError_t launch_eigen_coop(const EigArgs &args, hipStream_t st);
+int eigen_lds_width(int F);
+size_t eigen_lds_bytes(int F, int c);
+hipError_t launch_eigen_lds(const EigArgs &args, hipStream_t st);
+hipError_t launch_eigen_clear(int *status, int *bar, int *eflag, double2 *xbuf, int planes, int F,
+                              hipStream_t st);
 
 }  // namespace ulm

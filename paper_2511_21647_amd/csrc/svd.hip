@@ -758,12 +758,6 @@ __global__ __launch_bounds__(kEigThreads) void eigen_kernel(
     }
 }
 
-__global__ void clear_status_kernel(int *status, int *bar, int *eflag, int planes) {
-    if (threadIdx.x == 0) *status = 0;
-    for (int i = threadIdx.x; i < planes * kBarStride; i += blockDim.x) bar[i] = 0;
-    for (int i = threadIdx.x; i < planes; i += blockDim.x) eflag[i] = 0;
-}
-
 // ---------------------------------------------------------------- removal
 // I_f = I - (I V_c) V_c^H on v_mfma_f64_16x16x4f64, both products transposed so
 // that the pixel is the MFMA's N index (a tile is 16 consecutive pixels):
@@ -1148,8 +1142,9 @@ hipError_t launch_filter(const ulm_ctx *ctx, float2 *proj, double *eigvals_out, 
     double2 *C = (double2 *)(ws + w.cov);
     int *status = (int *)(ws + w.status);
 
-    hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(64), 0, st, status, (int *)(ws + w.bar),
-                       (int *)(ws + w.eflag), planes);
+    hipError_t e = launch_eigen_clear(status, (int *)(ws + w.bar), (int *)(ws + w.eflag),
+                                      (double2 *)(ws + w.xbuf), planes, F, st);
+    if (e != hipSuccess) return e;
     const int nwg = planes * w.gram_pairs * w.gram_chunks;
     if (ctx->cfg.precision == ULM_PREC_BF16X3)
         hipLaunchKernelGGL(gram_bf16x3_kernel, dim3(nwg), dim3(256), 0, st, proj, part, F, npix,
@@ -1157,14 +1152,16 @@ hipError_t launch_filter(const ulm_ctx *ctx, float2 *proj, double *eigvals_out, 
     else
         hipLaunchKernelGGL(gram_f64_kernel, dim3(nwg), dim3(256), 0, st, proj, part, F, npix,
                            w.gram_pairs, w.gram_chunks, w.gram_chunk_px, nblk);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(gram_reduce_kernel, dim3(planes * w.gram_pairs * (kGramBlock / kReduceRows)),
                        dim3(256), 0, st, part, C, F, w.gram_pairs, w.gram_chunks, nblk);
     if ((e = hipGetLastError()) != hipSuccess) return e;
 
     double *evals = (double *)(ws + w.evals);
-    if (eigen_coop_lds(F, c) <= 150 * 1024) {
+    // the split-precision form keeps the solver whose vectors' signs its rounding follows
+    // (eigen_lds.hip has the figures)
+    const bool split = ctx->cfg.precision == ULM_PREC_BF16X3;
+    if ((split ? eigen_lds_bytes(F, c) : eigen_coop_lds(F, c)) <= 150 * 1024) {
         EigArgs a;
         a.C = C;
         a.H = (double2 *)(ws + w.hvec);
@@ -1176,20 +1173,19 @@ hipError_t launch_filter(const ulm_ctx *ctx, float2 *proj, double *eigvals_out, 
         a.V = (double2 *)(ws + w.evecs);
         a.tscr = (double *)(ws + w.tscratch);
         a.xscr = (double2 *)(ws + w.xscratch);
-        a.vbuf = (double2 *)(ws + w.vbuf);
-        a.pbuf = (double2 *)(ws + w.pbuf);
+        a.xbuf = (double2 *)(ws + w.xbuf);
         a.bar = (int *)(ws + w.bar);
         a.flag = (int *)(ws + w.eflag);
         a.status = status;
         a.F = F;
         a.c = c;
-        a.W = eigen_coop_width(F);
+        a.W = split ? eigen_lds_width(F) : eigen_coop_width(F, planes);
         // diagnostic switch: the fenced exchange mode even where a plane's
         // work-groups share one XCD (the results are the same bit for bit)
         a.agent_scope = getenv("ULMPROJ_EIGEN_AGENT_SCOPE") != nullptr;
         a.planes = planes;
         a.plane0 = 0;
-        if ((e = launch_eigen_coop(a, st)) != hipSuccess) return e;
+        if ((e = split ? launch_eigen_lds(a, st) : launch_eigen_coop(a, st)) != hipSuccess) return e;
     } else {
         hipLaunchKernelGGL(eigen_kernel, dim3(planes), dim3(kEigThreads), 0, st, C,
                            (double2 *)(ws + w.tau), (double *)(ws + w.diag), (double *)(ws + w.offd),
