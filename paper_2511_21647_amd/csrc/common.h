@@ -156,6 +156,15 @@ __device__ inline int xcd_remap(int lin, int n) {
     return x * q + min(x, r) + s;
 }
 
+// Work-group barrier that orders LDS only: __syncthreads also waits for the wave's global
+// stores, which no other wave of these kernels reads.
+__device__ inline void lds_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 }  // namespace ulm
 
 struct ulm_ctx {

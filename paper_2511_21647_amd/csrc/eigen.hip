@@ -125,15 +125,6 @@ __device__ inline double2 add_conj_mul(double2 acc, double2 x, double2 v) {
     return make_double2(fma(x.y, v.y, fma(x.x, v.x, acc.x)), fma(-x.y, v.x, fma(x.x, v.y, acc.y)));
 }
 
-// Work-group barrier that orders LDS only: __syncthreads also waits for the wave's
-// global stores (the reflector's row), which nothing here reads.
-__device__ inline void lds_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
 constexpr unsigned kUnsetHi = 0x7ff8dead;       // upper word of an exchange slot not yet written
 __device__ inline double2 unset2() {
     const double u = __builtin_bit_cast(double, (unsigned long long)kUnsetHi << 32);

@@ -4,7 +4,9 @@
 // negative ones, H = (F - 1) / 2, each direction split by |frequency| into S
 // contiguous speed ranges), and the inverse DFT of each masked spectrum.
 //
-// sep_kernel: one work-group per (plane, 8 consecutive pixels).  The frames
+// sep_two_kernel: frame counts that split into two radices (all but five of those
+// supported); two passes with the butterflies in registers (see below).
+// sep_kernel: the others; one work-group per (plane, 8 consecutive pixels).  The frames
 // of those pixels are staged in LDS ([frame][pixel], pixels fastest, so the
 // global loads and stores are 64-byte rows and the butterflies read
 // consecutive banks), transformed by a mixed-radix Stockham FFT (radices 4, 2,
@@ -17,6 +19,7 @@
 #include <math.h>
 
 #include <cmath>
+#include <utility>
 #include <vector>
 
 namespace ulm {
@@ -36,6 +39,7 @@ struct SepArgs {
     unsigned pmag[kSepMaxPass];             // floor(2^32 / p) + 1 for the pass's p (0 when p = 1)
     int n_tw;                               // twiddle entries (all passes)
     const float2 *twt;                      // [n_tw + 21] twiddles, then the radix roots
+    const float2 *twf;                      // [F] exp(-2 pi i n / F), for the two-pass form
     int lo[kSepMaxSub], hi[kSepMaxSub];     // |k| range of each subset
 };
 
@@ -229,6 +233,230 @@ __global__ __launch_bounds__(kSepThreads) void sep_kernel(const float2 *__restri
     }
 }
 
+// ---------------------------------------------------------------- two-pass form
+// F = R1 R2 with both factors among kSepRadices: the transform is two passes whose
+// butterflies stay in registers.  With n = i + R2 q and k = m1 + R1 m2,
+//   X[k] = sum_i w_F^{i m1} [sum_q x[n] w_R1^{q m1}] w_R2^{i m2},
+// so thread (i, pixel) takes the R1 frames i + R2 q straight from memory, thread
+// (m1, pixel) ends with the R2 spectrum values m1 + R1 m2 and keeps them, and a
+// subset's inverse runs the same way back: its masked values through the R2-point
+// inverse in the registers that hold them, one exchange through LDS, the twiddles and
+// the R1-point inverse, and the frames straight to memory.  One LDS exchange a
+// transform (the general kernel: one a radix and the staging).
+// Bound by the stores: six subsets of 2 x 300 frames of 68500 pixels 1189 -> 552 us, of
+// which the loads and stores alone take 560 and all but the stores 380 (one or two
+// work-groups a CU overlap the two; consecutive work-groups on one XCD, whose L2 joins
+// the lines they share, 946 us without).  20 frames of 64 x 64 pixels 25 -> 11 us, 512 of
+// 150 x 200 1066 -> 450 us.
+
+// cos and sin of 2 pi q / R at compile time (Taylor series about the nearest octant's
+// multiple, in double)
+constexpr double sep_series(double x, bool odd) {
+    double term = odd ? x : 1.0, sum = term;
+    for (int n = odd ? 2 : 1; n < 40; n += 2) {
+        term *= -x * x / (double)(n * (n + 1));
+        sum += term;
+    }
+    return sum;
+}
+constexpr double kSepPi = 3.14159265358979323846264338327950288;
+constexpr double sep_cos(int q, int R) {
+    q %= R;
+    if (2 * q > R) return sep_cos(R - q, R);
+    if (4 * q > R) return -sep_cos(R - 2 * q, 2 * R);
+    if (8 * q > R) return sep_series(kSepPi * (R - 4 * q) / (2.0 * R), true);
+    return sep_series(2.0 * kSepPi * q / R, false);
+}
+constexpr double sep_sin(int q, int R) {
+    q %= R;
+    if (2 * q > R) return -sep_sin(R - q, R);
+    if (4 * q > R) return sep_sin(R - 2 * q, 2 * R);
+    if (8 * q > R) return sep_series(kSepPi * (R - 4 * q) / (2.0 * R), false);
+    return sep_series(2.0 * kSepPi * q / R, true);
+}
+
+template <int R> struct SepRoots {
+    float c[R], s[R];
+    constexpr SepRoots() : c(), s() {
+        for (int q = 0; q < R; ++q) {
+            c[q] = (float)sep_cos(q, R);
+            s[q] = (float)sep_sin(q, R);
+        }
+    }
+};
+
+// In-place R-point DFT in registers, as sep_dft; R = A B by A-point and B-point DFTs.
+template <int R, bool INV>
+__device__ inline void sep_reg_dft(float2 (&u)[R])
+{
+    if constexpr (R <= 5) {
+        sep_dft<R, INV>(u, nullptr);
+    } else if constexpr (R == 7) {
+        constexpr SepRoots<R> w;
+        float2 a[3], b[3], o[R];
+        o[0] = u[0];
+#pragma unroll
+        for (int q = 1; q <= 3; ++q) {
+            a[q - 1] = make_float2(u[q].x + u[R - q].x, u[q].y + u[R - q].y);
+            b[q - 1] = make_float2(u[q].x - u[R - q].x, u[q].y - u[R - q].y);
+            o[0].x += a[q - 1].x;
+            o[0].y += a[q - 1].y;
+        }
+#pragma unroll
+        for (int m = 1; m <= 3; ++m) {
+            float2 re = u[0], im = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int q = 1; q <= 3; ++q) {
+                re.x = fmaf(w.c[q * m % R], a[q - 1].x, re.x);
+                re.y = fmaf(w.c[q * m % R], a[q - 1].y, re.y);
+                im.x = fmaf(w.s[q * m % R], b[q - 1].x, im.x);
+                im.y = fmaf(w.s[q * m % R], b[q - 1].y, im.y);
+            }
+            const float2 t = mul_mi<INV>(im);
+            o[m] = make_float2(re.x + t.x, re.y + t.y);
+            o[R - m] = make_float2(re.x - t.x, re.y - t.y);
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) u[q] = o[q];
+    } else {
+        constexpr int A = R % 4 == 0 ? 4 : (R % 5 == 0 ? 5 : (R % 3 == 0 ? 3 : (R % 7 == 0 ? 7 : 2)));
+        constexpr int B = R / A;
+        constexpr SepRoots<R> w;
+        float2 v[A][B];
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            float2 x[A];
+#pragma unroll
+            for (int q = 0; q < A; ++q) x[q] = u[i + B * q];
+            sep_reg_dft<A, INV>(x);
+#pragma unroll
+            for (int m = 0; m < A; ++m) {
+                const float c = w.c[i * m], s = w.s[i * m];      // exp(-+ 2 pi i (i m) / R)
+                v[m][i] = i * m == 0 ? x[m]
+                          : INV ? make_float2(fmaf(x[m].x, c, -x[m].y * s), fmaf(x[m].x, s, x[m].y * c))
+                                : make_float2(fmaf(x[m].x, c, x[m].y * s), fmaf(-x[m].x, s, x[m].y * c));
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < A; ++m) {
+            sep_reg_dft<B, INV>(v[m]);
+#pragma unroll
+            for (int m2 = 0; m2 < B; ++m2) u[m + A * m2] = v[m][m2];
+        }
+    }
+}
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+// Pixels of a work-group: rows of 256 bytes (128-byte rows: 777 us where these took 605),
+// but 128 where a thread's second butterfly leaves too few registers for 32 pixels'
+// threads (512 frames, R2 = 32: 824 us with 256-byte rows, 450 so; R2 = 25 still 561
+// against 647).
+constexpr int sep_pixels(int r2) { return r2 <= 25 ? 32 : 16; }
+constexpr int sep_threads(int r2) { return (r2 * sep_pixels(r2) + 63) / 64 * 64; }
+
+template <int R1, int R2>
+__global__ __launch_bounds__(sep_threads(R2)) void sep_two_kernel(
+    const float2 *__restrict__ P, float2 *__restrict__ out, SepArgs g)
+{
+    constexpr int F = R1 * R2, kPix = sep_pixels(R2), kRow = R2 * kPix;
+    __shared__ float2 ex[R1][kRow];               // [m1][i][pixel]
+    const int groups = cdiv(g.npix, kPix);
+    const int lin = xcd_remap(blockIdx.x, groups * g.planes);
+    const int plane = lin / groups, px = threadIdx.x % kPix, i = threadIdx.x / kPix;
+    const int p = lin % groups * kPix + px;
+    const bool first = i < R2, second = i < R1;   // i is m1 in the second pass
+    // a plane through a descriptor: the frame's offset is scalar; pixels past the plane
+    // lie outside it, read as zero and are not stored
+    const int row = g.npix * (int)sizeof(float2);
+    const int off = p < g.npix && first ? i * row + p * (int)sizeof(float2) : -16;
+    const size_t at = (size_t)plane * F * g.npix;
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float2 *>(P + at), 0, F * row, 0x00027000);
+
+    __shared__ float2 tw[F];                      // exp(-2 pi i n / F)
+    for (int e = threadIdx.x; e < F; e += sep_threads(R2)) tw[e] = g.twf[e];
+    lds_barrier();
+    if (first) {
+        float2 u[R1];
+#pragma unroll
+        for (int q = 0; q < R1; ++q) {
+            const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(src, off, R2 * q * row, 0));
+            u[q] = make_float2(v[0], v[1]);
+        }
+        sep_reg_dft<R1, false>(u);
+#pragma unroll
+        for (int m = 0; m < R1; ++m) ex[m][i * kPix + px] = m == 0 ? u[m] : cmulf(u[m], tw[i * m]);
+    }
+    lds_barrier();
+    float2 X[R2];
+    if (second) {
+#pragma unroll
+        for (int n = 0; n < R2; ++n) X[n] = ex[i][n * kPix + px];
+        sep_reg_dft<R2, false>(X);
+    }
+    const float scale = 1.0f / (float)F;
+    const size_t sub_stride = (size_t)g.planes * F * g.npix;
+    for (int s = 0; s < g.n_sub; ++s) {
+        // bins [k0, k0 + n): lo.. up, or F - hi + 1.. down
+        const bool up = s < g.n_sub / 2;
+        const int n = g.hi[s] - g.lo[s], k0 = up ? g.lo[s] : F - g.hi[s] + 1;
+        lds_barrier();                          // the reads of the exchange before
+        if (second) {
+            float2 y[R2];
+#pragma unroll
+            for (int m = 0; m < R2; ++m) {
+                const bool keep = (unsigned)(i + R1 * m - k0) < (unsigned)n;
+                y[m] = keep ? X[m] : make_float2(0.f, 0.f);
+            }
+            sep_reg_dft<R2, true>(y);
+#pragma unroll
+            for (int m = 0; m < R2; ++m) ex[i][m * kPix + px] = y[m];
+        }
+        lds_barrier();
+        if (first) {
+            float2 u[R1];
+#pragma unroll
+            for (int m = 0; m < R1; ++m) {
+                const float2 v = ex[m][i * kPix + px];
+                u[m] = m == 0 ? v : cmulf_conj(v, tw[i * m]);
+            }
+            sep_reg_dft<R1, true>(u);
+            const __amdgpu_buffer_rsrc_t dst =
+                __builtin_amdgcn_make_buffer_rsrc(out + s * sub_stride + at, 0, F * row, 0x00027000);
+#pragma unroll
+            for (int q = 0; q < R1; ++q)
+                __builtin_amdgcn_raw_buffer_store_b64(
+                    __builtin_bit_cast(u32x2, f32x2{u[q].x * scale, u[q].y * scale}), dst, off, R2 * q * row, 0);
+        }
+    }
+}
+
+// The larger radices a butterfly is made for, and the smaller factor of the most even
+// split of F into two of them (0 if there is none).
+constexpr bool sep_is_radix(int r) {
+    constexpr int set[] = {2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 15, 16, 18, 20, 21, 24, 25, 27, 28, 32, 35};
+    for (int x : set)
+        if (x == r) return true;
+    return false;
+}
+constexpr int sep_split(int F) {
+    int best = 0;
+    for (int r = 2; r * r <= F; ++r)
+        if (F % r == 0 && sep_is_radix(r) && sep_is_radix(F / r)) best = r;
+    return best;
+}
+using SepKernel = void (*)(const float2 *, float2 *, SepArgs);
+template <int F> constexpr SepKernel sep_two_of() {
+    if constexpr (sep_split(F) != 0) return sep_two_kernel<sep_split(F), F / sep_split(F)>;
+    else return nullptr;
+}
+struct SepTable { SepKernel k[kSepMaxFrames + 1]; };
+template <int... Fs> constexpr SepTable sep_two_table(std::integer_sequence<int, Fs...>) {
+    return {{sep_two_of<Fs>()...}};
+}
+
 // Radices for F (4 first, then 2, 3, 5, 7); false if F has another prime factor.
 static bool sep_factor(int F, SepArgs &g) {
     g.n_pass = 0;
@@ -258,7 +486,8 @@ bool separate_supported(int F) {
 // The kernel's table for F frames: tw[tw_off[s] + k R + q] = exp(-2 pi i q k /
 // (p R)) for every pass s (radix R, p = product of the earlier radices), then
 // the roots exp(-2 pi i q / R) of R = 2, 3, 4, 5, 7 (2 + 3 + 4 + 5 + 7 = 21
-// entries); FP64, rounded to FP32.  Empty if F is not supported.
+// entries), then exp(-2 pi i n / F) of n < F for the two-pass form; FP64, rounded to
+// FP32.  Empty if F is not supported.
 std::vector<float2> separate_twiddles(int F) {
     SepArgs g;
     if (!separate_supported(F)) return {};
@@ -280,6 +509,7 @@ std::vector<float2> separate_twiddles(int F) {
     int o = g.n_tw;
     for (int r : rad)
         for (int q = 0; q < r; ++q) t[o++] = root(-(double)q / (double)r);
+    for (int n = 0; n < F; ++n) t.push_back(root(-(double)n / (double)F));
     return t;
 }
 
@@ -307,6 +537,17 @@ hipError_t launch_separate(const ulm_ctx *ctx, const float2 *P, int n_speed, flo
         }
     g.twt = ctx->tab.sep_tw;
     if (!g.twt) return hipErrorInvalidValue;
+    g.twf = g.twt + g.n_tw + 21;
+    // two passes where the frames split into two radices and a plane fits a descriptor's
+    // 31-bit offsets; the general kernel otherwise (2, 3, 5, 7 and 343 frames)
+    static constexpr auto two = sep_two_table(std::make_integer_sequence<int, kSepMaxFrames + 1>());
+    const int r1 = sep_split(g.F);
+    if (r1 && (size_t)g.F * g.npix * sizeof(float2) < (1ull << 31) - 4096) {
+        const int r2 = g.F / r1;
+        hipLaunchKernelGGL(two.k[g.F], dim3(cdiv(g.npix, sep_pixels(r2)) * g.planes), dim3(sep_threads(r2)), 0,
+                           st, P, out, g);
+        return hipGetLastError();
+    }
     const int groups = cdiv(g.npix, kSepPix);
     hipLaunchKernelGGL(sep_kernel, dim3(groups * g.planes), dim3(kSepThreads),
                        separate_lds_bytes(g.F), st, P, out, g);
