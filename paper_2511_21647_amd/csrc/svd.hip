@@ -15,10 +15,13 @@
 #include <float.h>
 #include <stdlib.h>
 
+#include <type_traits>
+
 namespace ulm {
 
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -40,8 +43,132 @@ __device__ inline void pair_of(int pair, int nblk, int &I, int &J) {
 //   C_re += A . B      with A[f][k], B[k][f'] = (re, im) of pixel p
 //   C_im += A . B'     with B'[k][f'] = (im, -re)
 // FP32 inputs are exact in FP64, so every product is exact and only FP64
-// summation rounds.
-__global__ __launch_bounds__(256) void gram_f64_kernel(const float2 *__restrict__ P,
+// summation rounds.  Tiles past frame F and those below the diagonal of a diagonal
+// block are not formed, and what is left is dealt evenly to the waves (300 frames: 198
+// tiles of work where 220 were), the pixels in flight come through descriptors, which
+// leaves registers for three waves a SIMD: 70 planes of 300 x 68500 39.1 -> 33.0 ms (the
+// products of 190 tiles at the rate of a large FP64 matrix product take 28), 2 planes of 20
+// x 4096 14 -> 7.3 us.
+
+// One work-group's block: N tiles a wave (the four of a quadrant, whose tiles share
+// operands, or up to three single ones).  BUF: the block's rows fit a descriptor.
+template <int N, bool BUF>
+__device__ inline void gram_f64_block(const float2 *__restrict__ src, double2 *__restrict__ dst, int F, int npix,
+                                      int px0, int px1, int I, int J, int n, int nc, int wave,
+                                      float2 (&lds)[2 * kGramBlock][kGramStage + 1])
+{
+    const int lane = threadIdx.x & 63;
+    const int kk = lane >> 4, r16 = lane & 15;
+    // rows and columns of the wave's tiles; past the last one that one again
+    int tr[N], tc[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        if constexpr (N == 4) {
+            tr[q] = (wave >> 1) * 2 + (q >> 1);
+            tc[q] = (wave & 1) * 2 + (q & 1);
+        } else {
+            int e = min(wave * N + q, n - 1);
+            if (I == J) {
+                int r = 0;
+                for (; e >= nc - r; ++r) e -= nc - r;
+                tr[q] = r;
+                tc[q] = r + e;
+            } else {
+                tr[q] = e / nc;
+                tc[q] = e % nc;
+            }
+        }
+    }
+
+    f64x4 accr[N], acci[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) accr[q] = acci[q] = f64x4{0, 0, 0, 0};
+
+    // the next stage's pixels are loaded into registers while this stage's
+    // products run
+    constexpr int kPer = 2 * kGramBlock * kGramStage / 256, kRowsPer = 256 / kGramStage;
+    const int row = BUF ? npix * (int)sizeof(float2) : 0;
+    // a descriptor for each block's frames: those past frame F lie outside it and read as
+    // zero, and so do pixels past the chunk
+    auto rows_of = [&](int b) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float2 *>(src) + (size_t)b * kGramBlock * npix, 0,
+                                                 min(kGramBlock, F - b * kGramBlock) * row, 0x00027000);
+    };
+    const __amdgpu_buffer_rsrc_t ri = rows_of(I), rj = rows_of(J);
+    const int srow = threadIdx.x / kGramStage, scol = threadIdx.x % kGramStage;
+    f32x2 pre[kPer];
+    auto fetch = [&](int p0) {
+        const bool in = p0 + scol < px1;
+        const int off = in ? srow * row + (p0 + scol) * (int)sizeof(float2) : (int)0x80000000;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int r = i % (kPer / 2) * kRowsPer;
+            if constexpr (BUF) {
+                pre[i] = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(
+                                                       i < kPer / 2 ? ri : rj, off + r * row, 0, 0));
+            } else {
+                const int frame = (i < kPer / 2 ? I : J) * kGramBlock + srow + r;
+                pre[i] = f32x2{0.f, 0.f};
+                if (in && frame < F) {
+                    const float2 v = src[(size_t)frame * npix + p0 + scol];
+                    pre[i] = f32x2{v.x, v.y};
+                }
+            }
+        }
+    };
+    fetch(px0);
+    for (int p0 = px0; p0 < px1; p0 += kGramStage) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int e = threadIdx.x + 256 * i;
+            lds[e / kGramStage][e % kGramStage] = make_float2(pre[i][0], pre[i][1]);
+        }
+        __syncthreads();
+        if (p0 + kGramStage < px1) fetch(p0 + kGramStage);
+#pragma unroll
+        for (int step = 0; step < kGramStage / 2; ++step) {
+            const int pxl = step * 2 + (kk >> 1);
+            const bool im = kk & 1;
+            double a[N], br[N], bi[N];
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                if (N < 4 || q % 2 == 0) {
+                    const float2 v = lds[tr[q] * 16 + r16][pxl];
+                    a[q] = im ? v.y : v.x;
+                } else {
+                    a[q] = a[q - 1];
+                }
+                if (N < 4 || q < 2) {
+                    const float2 v = lds[kGramBlock + tc[q] * 16 + r16][pxl];
+                    br[q] = im ? v.y : v.x;
+                    bi[q] = im ? -v.x : v.y;
+                } else {
+                    br[q] = br[q - 2];
+                    bi[q] = bi[q - 2];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                accr[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], br[q], accr[q], 0, 0, 0);
+                acci[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], bi[q], acci[q], 0, 0, 0);
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        if (N < 4 && wave * N + q >= n) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            // v_mfma_f64_16x16x4f64 result: lane l, register r holds D[4 r + l / 16][l % 16]
+            const int row = tr[q] * 16 + 4 * r + kk, col = tc[q] * 16 + r16;
+            dst[row * kGramBlock + col] = make_double2(accr[q][r], acci[q][r]);
+        }
+    }
+}
+
+template <bool BUF>
+__global__ __launch_bounds__(256, 2) void gram_f64_kernel(const float2 *__restrict__ P,
                                                        double2 *__restrict__ part, int F,
                                                        int npix, int pairs, int chunks, int chunk_px,
                                                        int nblk)
@@ -59,89 +186,20 @@ __global__ __launch_bounds__(256) void gram_f64_kernel(const float2 *__restrict_
     const int px1 = min(px0 + chunk_px, npix);
 
     __shared__ float2 lds[2 * kGramBlock][kGramStage + 1];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wi = wave >> 1, wj = wave & 1;
-    // in a diagonal block the lower-left quadrant mirrors the upper-right one
-    // (C is Hermitian, and the reduction reads it from there): its wave only
-    // stages pixels
-    const bool mirror = I == J && wi == 1 && wj == 0;
-    const int kk = lane >> 4, r16 = lane & 15;
-
-    f64x4 accr[2][2], acci[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            accr[a][b] = f64x4{0, 0, 0, 0};
-            acci[a][b] = f64x4{0, 0, 0, 0};
-        }
-
-    // the next stage's pixels are loaded into registers while this stage's
-    // products run
-    constexpr int kPer = 2 * kGramBlock * kGramStage / 256;
-    float2 pre[kPer];
-    auto fetch = [&](int p0) {
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            const int e = threadIdx.x + 256 * i;
-            const int row = e / kGramStage, col = e % kGramStage;
-            const int frame = row < kGramBlock ? I * kGramBlock + row : J * kGramBlock + row - kGramBlock;
-            const int px = p0 + col;
-            pre[i] = make_float2(0.f, 0.f);
-            if (frame < F && px < px1) pre[i] = src[(size_t)frame * npix + px];
-        }
-    };
-    fetch(px0);
-    for (int p0 = px0; p0 < px1; p0 += kGramStage) {
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            const int e = threadIdx.x + 256 * i;
-            lds[e / kGramStage][e % kGramStage] = pre[i];
-        }
-        __syncthreads();
-        if (p0 + kGramStage < px1) fetch(p0 + kGramStage);
-        // the mirror wave of a diagonal block forms nothing; the others' 16
-        // steps are unrolled whole (a static trip count)
-        if (!mirror)
-#pragma unroll
-        for (int step = 0; step < kGramStage / 2; ++step) {
-            const int pxl = step * 2 + (kk >> 1);
-            const bool im = kk & 1;
-            double a[2], br[2], bi[2];
-#pragma unroll
-            for (int ti = 0; ti < 2; ++ti) {
-                const float2 v = lds[wi * 32 + ti * 16 + r16][pxl];
-                a[ti] = im ? v.y : v.x;
-            }
-#pragma unroll
-            for (int tj = 0; tj < 2; ++tj) {
-                const float2 v = lds[kGramBlock + wj * 32 + tj * 16 + r16][pxl];
-                br[tj] = im ? v.y : v.x;
-                bi[tj] = im ? -v.x : v.y;
-            }
-#pragma unroll
-            for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-                for (int tj = 0; tj < 2; ++tj) {
-                    accr[ti][tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ti], br[tj], accr[ti][tj], 0, 0, 0);
-                    acci[ti][tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ti], bi[tj], acci[ti][tj], 0, 0, 0);
-                }
-        }
-        __syncthreads();
-    }
-
+    // the waves change places from work-group to work-group, so that blocks whose last
+    // wave has fewer tiles do not always idle the same SIMD
+    const int wave = __builtin_amdgcn_readfirstlane(((threadIdx.x >> 6) + wl / pairs + pair) & 3);
+    // tiles of 16 x 16 of the block that are formed: not those past frame F, and in a
+    // diagonal block not those below the diagonal (C is Hermitian; the reduction mirrors
+    // them).  A whole block's 16 go by quadrants to the waves, fewer row by row in equal
+    // shares.
+    const int nc = min(4, cdiv(F - J * kGramBlock, 16));
+    const int n = I == J ? nc * (nc + 1) / 2 : 4 * nc;
     double2 *dst = part + ((size_t)(plane * pairs + pair) * chunks + chunk) * kGramBlock * kGramBlock;
-#pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 2; ++tj)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                // v_mfma_f64_16x16x4f64 result: lane l, register r holds D[4 r + l / 16][l % 16]
-                const int row = wi * 32 + ti * 16 + 4 * r + kk;
-                const int col = wj * 32 + tj * 16 + r16;
-                dst[row * kGramBlock + col] = make_double2(accr[ti][tj][r], acci[ti][tj][r]);
-            }
+    if (n > 12) gram_f64_block<4, BUF>(src, dst, F, npix, px0, px1, I, J, n, nc, wave, lds);
+    else if (n > 8) gram_f64_block<3, BUF>(src, dst, F, npix, px0, px1, I, J, n, nc, wave, lds);
+    else if (n > 4) gram_f64_block<2, BUF>(src, dst, F, npix, px0, px1, I, J, n, nc, wave, lds);
+    else gram_f64_block<1, BUF>(src, dst, F, npix, px0, px1, I, J, n, nc, wave, lds);
 }
 
 // Three-term BF16 split of a value (hi, mid, lo).
@@ -167,7 +225,6 @@ __device__ inline bf16x3 split3(double x) {
     return o;
 }
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 struct bf16x2x3 { bf16x2 h, m, l; };
 
@@ -363,12 +420,13 @@ __global__ __launch_bounds__(256, 2) void gram_bf16x3_kernel(const float2 *__res
 // I <= J, 4 rows of the 64 x 64 block): thread (row, column) adds its element
 // over the pixel chunks in chunk order, so a row of 64 partials is one
 // contiguous read, and writes it to C with its mirror: the conjugate into
-// block (J, I), and in a diagonal block the upper-right quadrant's conjugate
-// into the lower-left one (whose partials the Gram kernels do not form).
+// block (J, I), and in a diagonal block the tiles above the diagonal conjugated
+// into those below, which the Gram kernels do not form (tiles of `tile` rows: 16
+// in FP64, a quadrant's 32 in BF16).
 constexpr int kReduceRows = 4;
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const double2 *__restrict__ part,
                                                           double2 *__restrict__ C, int F, int pairs,
-                                                          int chunks, int nblk)
+                                                          int chunks, int nblk, int tile)
 {
     constexpr int kStrips = kGramBlock / kReduceRows;
     const int strip = blockIdx.x % kStrips;
@@ -378,7 +436,7 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double2 *__restr
     pair_of(pair, nblk, I, J);
     const int r = strip * kReduceRows + (threadIdx.x >> 6), c = threadIdx.x & 63;
     const bool diag = I == J;
-    if (diag && r >= kGramBlock / 2 && c < kGramBlock / 2) return;
+    if (diag && r / tile > c / tile) return;
     const int f1 = I * kGramBlock + r, f2 = J * kGramBlock + c;
     if (f1 >= F || f2 >= F) return;
     const double2 *src = part + (size_t)(plane * pairs + pair) * chunks * kGramBlock * kGramBlock +
@@ -392,7 +450,7 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double2 *__restr
     }
     double2 *Cp = C + (size_t)plane * F * F;
     Cp[(size_t)f1 * F + f2] = make_double2(re, im);
-    if (!diag || (r < kGramBlock / 2 && c >= kGramBlock / 2)) Cp[(size_t)f2 * F + f1] = make_double2(re, -im);
+    if (!diag || r / tile < c / tile) Cp[(size_t)f2 * F + f1] = make_double2(re, -im);
 }
 
 // ---------------------------------------------------------------- eigensolver
@@ -1146,21 +1204,23 @@ hipError_t launch_filter(const ulm_ctx *ctx, float2 *proj, double *eigvals_out, 
                                       (double2 *)(ws + w.xbuf), planes, F, st);
     if (e != hipSuccess) return e;
     const int nwg = planes * w.gram_pairs * w.gram_chunks;
-    if (ctx->cfg.precision == ULM_PREC_BF16X3)
+    const bool split = ctx->cfg.precision == ULM_PREC_BF16X3;
+    if (split)
         hipLaunchKernelGGL(gram_bf16x3_kernel, dim3(nwg), dim3(256), 0, st, proj, part, F, npix,
                            w.gram_pairs, w.gram_chunks, w.gram_chunk_px, nblk);
     else
-        hipLaunchKernelGGL(gram_f64_kernel, dim3(nwg), dim3(256), 0, st, proj, part, F, npix,
+        // 64 rows of a plane within a descriptor's 31-bit offsets, or plain addresses
+        hipLaunchKernelGGL((npix < (1 << 22) ? gram_f64_kernel<true> : gram_f64_kernel<false>), dim3(nwg), dim3(256), 0, st, proj, part, F, npix,
                            w.gram_pairs, w.gram_chunks, w.gram_chunk_px, nblk);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(gram_reduce_kernel, dim3(planes * w.gram_pairs * (kGramBlock / kReduceRows)),
-                       dim3(256), 0, st, part, C, F, w.gram_pairs, w.gram_chunks, nblk);
+                       dim3(256), 0, st, part, C, F, w.gram_pairs, w.gram_chunks, nblk,
+                       split ? 32 : 16);
     if ((e = hipGetLastError()) != hipSuccess) return e;
 
     double *evals = (double *)(ws + w.evals);
     // the split-precision form keeps the solver whose vectors' signs its rounding follows
     // (eigen_lds.hip has the figures)
-    const bool split = ctx->cfg.precision == ULM_PREC_BF16X3;
     if ((split ? eigen_lds_bytes(F, c) : eigen_coop_lds(F, c)) <= 150 * 1024) {
         EigArgs a;
         a.C = C;

@@ -37,3 +37,10 @@ def test_filter_short_chunks(F, nz, nu, c, precision):
     # the tolerances of the filter's other comparisons
     assert e <= (2e-5 if precision == "fp64" else 1e-3)
     assert el <= (1e-10 if precision == "fp64" else 1e-6)
+
+
+@pytest.mark.parametrize("F", [1, 16, 17, 48, 49, 64, 80, 81, 96, 112, 113, 128, 145])
+def test_filter_gram_tiles(F):
+    """The FP64 Gram's tile shares: every number of 16-frame tiles in the last block, on and
+    off the diagonal."""
+    test_filter_short_chunks(F, 16, 33, min(F, 3), "fp64")
