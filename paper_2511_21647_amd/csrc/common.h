@@ -40,6 +40,7 @@ struct Removal64Dims {
     int KS1;           // K-steps of I V_c: (re, im) per 4 frames
     int FT;            // 8-frame tiles of the output
     int KS2;           // K-steps (4 real rows each, all MT tiles) of (I V_c) V_c^H
+    int KU;            // those of them that hold any of the 2c rows
     size_t t1_plane;   // doubles per plane, first product
     size_t t2_plane;   // doubles per plane, second product
 };
@@ -49,6 +50,7 @@ inline Removal64Dims removal64_dims(int F, int c) {
     d.KS1 = 2 * ((F + 3) / 4);
     d.FT = (F + 7) / 8;
     d.KS2 = 4 * d.MT;
+    d.KU = (2 * c + 3) / 4;
     d.t1_plane = (size_t)d.MT * d.KS1 * 64;
     d.t2_plane = (size_t)d.FT * d.KS2 * 64;
     return d;

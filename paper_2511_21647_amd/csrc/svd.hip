@@ -870,9 +870,13 @@ __global__ void removal_f64_tables_kernel(const double2 *__restrict__ V, double 
     tab[(size_t)plane * (n1 + n2) + e] = val;
 }
 
+// Bound by the products and the traffic together (70 planes of 300 x 68500, cutoff 20:
+// the plane is read twice and written once, 34.5 GB, 6.9 ms at a copy's rate; the
+// products of 48 of Y^T's rows 8.2 ms): 12.5 ms with two tiles and whole row tiles in the
+// second product, 11.3 with three and without its zero rows (four tiles 11.6).
 // A wave owns kRemNT tiles of 16 pixels (the table operands are shared by them);
 // MT = tiles of 16 rows of Y^T.
-constexpr int kRemNT = 2;
+constexpr int kRemNT = 3;
 constexpr int kRemAhead = 4;       // frame groups of the plane in flight
 template <int MT>
 __global__ __launch_bounds__(256) void removal_f64_kernel(float2 *__restrict__ P,
@@ -970,6 +974,7 @@ __global__ __launch_bounds__(256) void removal_f64_kernel(float2 *__restrict__ P
                 for (int T = 0; T < MT; ++T)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
+                        if (T == MT - 1 && r > 0 && 4 * T + r >= d.KU) break;     // zero rows
                         const double a = w2[(size_t)(4 * T + r) * 64];
 #pragma unroll
                         for (int nt = 0; nt < kRemNT; ++nt)
