@@ -1021,9 +1021,11 @@ __global__ void cnn_loss_final_kernel(const double *__restrict__ part, int n, do
 // k and 16 pixels in registers (head_group's product from LDS), which is where the
 // target is read 128 bytes a pixel and what the weight gradient's A operand needs;
 // g goes through LDS once to put the pixel in the lane for the data gradient.  Both
-// gradients are products on v_mfma_f32_32x32x2f32: g stays in FP32.  A K-step takes
-// index 8 a + b of the lower half-wave and 8 a + 4 + b of the upper, the order in
-// which a result's registers hold its rows.
+// gradients are products on v_mfma_f32_32x32x2f32: g stays in FP32.  In the weight
+// gradient a K-step takes pixel 8 a + b of the lower half-wave and 8 a + 4 + b of the
+// upper, the order in which a result's registers hold its rows; in the data gradient k
+// runs in order through one sum, whose bits (the instruction is a chain of two fused
+// sums) decide how dz6 rounds to BF16: two sums moved a small image's gradients by 5e-5.
 // Bound by HBM (target 256 B, activations 64 B read and 64 B written a pixel in
 // BF16) and by the 4100 cycles of FP32 matrix products per 32 pixels, about alike.
 // As five kernels (logits and g through HBM, the weight gradient with one FMA per
@@ -1128,19 +1130,16 @@ __global__ __launch_bounds__(64 * kHtWaves, 2) void cnn_head_train_kernel(
                 dw[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(g[nb][q], a, dw[nb], 0, 0, 0);
         }
         __builtin_amdgcn_wave_barrier();
-        // data gradient: rows c, columns pixels
-        f32x16 dz[2] = {{}, {}};
+        // data gradient: rows c, columns pixels; k in order, one sum
+        f32x16 dz = {};
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
+        for (int u = 0; u < kR2 / 4; ++u) {
+            const float4 v = *reinterpret_cast<const float4 *>(gs + i32 * kHtGs + 4 * u);
+            const float gv[2] = {hk ? v.y : v.x, hk ? v.w : v.z};
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const float4 v = *reinterpret_cast<const float4 *>(gs + i32 * kHtGs + 32 * nb + 8 * a + 4 * hk);
-                const float gv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    dz[b & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                        wf[(32 * nb + 8 * a + 4 * hk + b) * kC + i32], gv[b], dz[b & 1], 0, 0, 0);
-            }
+            for (int b = 0; b < 2; ++b)
+                dz = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[(4 * u + 2 * b + hk) * kC + i32], gv[b], dz, 0, 0, 0);
+        }
         // lane: pixel i32, register q: channel 8 (q / 4) + 4 hk + q % 4
         if (i32 < np) {
 #pragma unroll
@@ -1150,7 +1149,7 @@ __global__ __launch_bounds__(64 * kHtWaves, 2) void cnn_head_train_kernel(
                 for (int b = 0; b < 4; ++b) {
                     const int c = 8 * a + 4 * hk + b;
                     const bool on = tof(as[i32 * PS + c]) > 0.f;
-                    o[b] = fromf<T>(on ? dz[0][4 * a + b] + dz[1][4 * a + b] : 0.f);
+                    o[b] = fromf<T>(on ? dz[4 * a + b] : 0.f);
                 }
                 T *dst = dz6 + (p0 + i32) * kC + 8 * a + 4 * hk;
                 if constexpr (sizeof(T) == 2) *reinterpret_cast<uint2 *>(dst) = *reinterpret_cast<const uint2 *>(o);
