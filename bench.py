@@ -320,7 +320,7 @@ def time_separation(cfg, ctx, args):
     del planes, subs
     torch.cuda.empty_cache()
     return {"ms_per_ensemble": round(ms, 3), "subsets": 2 * SEPARATION_SPEEDS,
-            "roofline": {"bound": "hbm", "kernel": "sep_kernel", "achieved": round(gbs, 1),
+            "roofline": {"bound": "hbm", "kernel": "sep_two_kernel", "achieved": round(gbs, 1),
                          "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4),
                          "algorithmic_bytes": nbytes}}
 
@@ -742,12 +742,13 @@ def _kernel_work(name, wgs, gy, gz):
         planes = gy
         return ("hbm", 2 * planes * plane_bytes, "byte", HBM_PEAK_GBS / 1e3,
                 f"{planes} planes read and written once")
-    if "stage2_fir_kernel" in short:
-        planes = 2 * (35 if "<4>" in short else 1)
+    if "stage2_fir_kernel" in short or "stage2_slab_kernel" in short:
+        planes = 2 * (35 if "slab" in short else 1)
         return ("hbm", 2 * K_P * F_P * NPIX_P * 8 + planes * plane_bytes, "byte",
                 HBM_PEAK_GBS / 1e3, f"slices read once, {planes} planes written")
-    if "frame_max_kernel" in short or "ncc_band_kernel" in short:
-        planes = gz if "ncc_band" in short else max(1, round(wgs / F_P))    # one work-group per image
+    if "frame_max_kernel" in short or "ncc_stream_kernel" in short:
+        # one work-group per image, or one per band of 38 rows
+        planes = max(1, round(wgs / (F_P * (7 if "ncc_stream" in short else 1))))
         return ("hbm", planes * plane_bytes, "byte", HBM_PEAK_GBS / 1e3, f"{planes} planes read once")
     if "cnn_conv_kernel" in short:
         # the launch grid is the same for every batch; the median launch is a
@@ -760,7 +761,7 @@ def _kernel_work(name, wgs, gy, gz):
         return ("hbm", 2 * plane_bytes, "byte", HBM_PEAK_GBS / 1e3, "2 planes written")
     if "xdoppler_kernel" in short:
         return ("hbm", 3 * 2 * plane_bytes, "byte", HBM_PEAK_GBS / 1e3, "2 x 2 planes read, 2 written")
-    if "sep_kernel" in short:
+    if "sep_two_kernel" in short or "sep_kernel" in short:
         return ("hbm", 7 * 2 * plane_bytes, "byte", HBM_PEAK_GBS / 1e3, "2 planes read, 6 x 2 written")
     if "mot_corr_kernel" in short:
         return ("mfma", 2.0 * 2 * K_P * F_P * 289 * NPIX_P, "flop", FP32_MFMA_PEAK_TFLOPS,
