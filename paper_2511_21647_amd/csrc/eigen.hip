@@ -25,7 +25,7 @@
 // two reciprocals, and one trip through the XCD's L2.  Against columns in LDS, a work-group
 // barrier for each of a step's sums and a flag barrier for its exchange (eigen_lds.hip):
 // 2 planes of 300 frames 2013 -> 1061 us (the reduction 1233 -> 750), 70 planes 10.8 ->
-// 4.65 ms, 2 planes of 20 frames 120 -> 72 us.
+// 4.65 ms, 2 planes of 20 frames 120 -> 66 us.
 // Waits are bounded: a wave that waits too long flags the status word and exits, so
 // every wave always finishes.
 #include "eigen_exchange.h"
@@ -484,9 +484,9 @@ __global__ __launch_bounds__(kCoopThreads, NR <= 6 ? 2 : 1) void eigen_coop_kern
     }
     if (!plane_barrier(flags, w, W, ++nbar, &abort_s, a.status, bmode)) return;
 
-    // 2. every eigenvalue by multisection on Sturm counts: a group of kPoints
-    //    lanes per eigenvalue counts at kPoints interior points of its bracket,
-    //    so each round narrows the bracket (kPoints + 1)-fold.  The count is the sign
+    // 2. every eigenvalue by multisection on Sturm counts: a group of `pts`
+    //    lanes per eigenvalue counts at as many interior points of its bracket, so each
+    //    round narrows the bracket (pts + 1)-fold.  The count is the sign
     //    changes of the leading minors' sequence p_i = (d_i - x) p_{i-1} - e_{i-1}^2
     //    p_{i-2}, whose chain is one FMA a row (the quotient form's is a reciprocal
     //    and three); T is scaled by a power of two to a norm near 1 and the sequence
@@ -520,8 +520,11 @@ __global__ __launch_bounds__(kCoopThreads, NR <= 6 ? 2 : 1) void eigen_coop_kern
     __syncthreads();
     double *lam = a.lam + (size_t)plane * F;
     constexpr int kScaleRows = 8;
-    for (int idx0 = ra.gw * kGroups; idx0 < F; idx0 += ra.nwv * kGroups) {
-        const int g = lane / kPoints, pi = lane % kPoints;
+    // 16 points, or where four waves would then pass over the eigenvalues twice or more
+    // so few that one pass does (20 frames: 17 rounds instead of 2 x 13)
+    const int lp = NR > 1 || F <= 16 ? 4 : (F <= 32 ? 3 : 2), pts = 1 << lp, groups = 64 >> lp;
+    for (int idx0 = ra.gw * groups; idx0 < F; idx0 += ra.nwv * groups) {
+        const int g = lane >> lp, pi = lane & (pts - 1);
         const int idx = idx0 + g;
         const bool mine = idx < F;
         const int target = F - 1 - idx;                   // eigenvalues below this one
@@ -530,7 +533,7 @@ __global__ __launch_bounds__(kCoopThreads, NR <= 6 ? 2 : 1) void eigen_coop_kern
         for (int it = 0; it < 200; ++it) {
             if (act && hi - lo <= 2.0 * DBL_EPSILON * tnorm) act = false;
             if (__ballot(act) == 0ull) break;
-            const double x = lo + (hi - lo) * (double)(pi + 1) / (double)(kPoints + 1);
+            const double x = lo + (hi - lo) * (double)(pi + 1) / (double)(pts + 1);
             const double xs = ldexp(x, tex);
             double p0 = 1.0, p1 = sde[0].x - xs, e2 = sde[0].y;
             int cnt = __double2hiint(p1) < 0;
@@ -558,11 +561,11 @@ __global__ __launch_bounds__(kCoopThreads, NR <= 6 ? 2 : 1) void eigen_coop_kern
             // counts grow with x: the eigenvalue lies between the last point
             // below and the first point above
             const unsigned long long m = __ballot(cnt > target);
-            const unsigned bits = (unsigned)((m >> (g * kPoints)) & ((1ull << kPoints) - 1ull));
-            const int first = bits ? __ffs(bits) - 1 : kPoints;
-            const double nlo = __shfl(x, g * kPoints + (first > 0 ? first - 1 : 0));
-            const double nhi = __shfl(x, g * kPoints + (first < kPoints ? first : kPoints - 1));
-            const double lo2 = first > 0 ? nlo : lo, hi2 = first < kPoints ? nhi : hi;
+            const unsigned bits = (unsigned)((m >> (g * pts)) & ((1ull << pts) - 1ull));
+            const int first = bits ? __ffs(bits) - 1 : pts;
+            const double nlo = __shfl(x, g * pts + (first > 0 ? first - 1 : 0));
+            const double nhi = __shfl(x, g * pts + (first < pts ? first : pts - 1));
+            const double lo2 = first > 0 ? nlo : lo, hi2 = first < pts ? nhi : hi;
             if (act && lo2 == lo && hi2 == hi) act = false;
             if (act) {
                 lo = lo2;

@@ -2,7 +2,8 @@
 // plane's Casorati matrix I (pixels x frames):
 //   1. covariance C = I^H I   (gram_f64_kernel + gram_reduce_kernel, FP64 MFMA;
 //      gram_bf16x3_kernel for the split-precision form)
-//   2. eigendecomposition of C in FP64 (eigen_kernel: Householder
+//   2. eigendecomposition of C in FP64 (eigen.hip, eigen_lds.hip; eigen_kernel where those
+//      do not fit: Householder
 //      tridiagonalisation, bisection on Sturm counts, inverse iteration for the
 //      clutter eigenvectors, back-transformation)
 //   3. removal I_f = I - (I V_c) V_c^H   (removal_f64_kernel, FP64 MFMA;
