@@ -24,6 +24,7 @@
 //   mot_mean_kernel   per-orientation means and the 3D motion per frame
 #include "common.h"
 #include "roots.h"
+#include "windows.h"
 
 #include <math.h>
 
@@ -31,10 +32,7 @@ namespace ulm {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kMotFrames = 32;     // frames per work-group: the MFMA's M
-constexpr int kMotRows = 16;       // slice rows per work-group
-constexpr int kMotStage = 128;     // pixels staged in LDS per step
-constexpr int kMotFly = kMotFrames * kMotStage / 256;   // of those, values per thread
+constexpr int kMotFly = kMotFrames * kMotStage / 256;   // staged values per thread and step
 constexpr int kMotAS = kMotStage + 1;
 constexpr int kMotMaxLag = 10;     // lag window |dz|, |du| <= L, L <= 10
 
@@ -140,22 +138,19 @@ __global__ __launch_bounds__(256, NT <= 10 ? 3 : 2) void mot_corr_kernel(const f
 
     const int npx = rows * a.nu;
     const int f0 = fb * kMotFrames;
-    // the frames' values through a buffer descriptor on frame f0 from the band's first
-    // row on: a frame's scalar offset plus the pixel's, zeros past the last frame and,
-    // by an offset outside it, past the band's pixels
-    const int frame_bytes = a.npix * (int)sizeof(float2);
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(S + ((size_t)s * a.F + f0) * a.npix + (size_t)z0 * a.nu), 0,
-        min(a.F - f0, kMotFrames) * frame_bytes - z0 * a.nu * (int)sizeof(float2), 0x00027000);
     // the next step's values of this thread (one pixel, half of the frames), in flight
-    // during the MFMAs
+    // during the MFMAs: each frame's band through a descriptor of its own, which has no
+    // values of a frame past the last or of pixels past the band (they read as zero)
     const int tp = t % kMotStage, tf = __builtin_amdgcn_readfirstlane(t / kMotStage) * kMotFly;
     float2 xa[kMotFly];
     auto fetch = [&](int p0n) {
-        const int p = p0n + tp, off = p < npx ? p * (int)sizeof(float2) : 0x7ffffff0;
+        const int p = p0n + tp;
 #pragma unroll
         for (int i = 0; i < kMotFly; ++i) {
-            const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, off, (tf + i) * frame_bytes, 0);
+            const Window win = mot_window(s, a.F, f0 + tf + i, a.nz, a.nu, z0, rows);
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc((void *)(S + win.at), 0, win.bytes, 0x00027000);
+            const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, p * (int)sizeof(float2), 0, 0);
             xa[i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
         }
     };
