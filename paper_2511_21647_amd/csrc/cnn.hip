@@ -21,6 +21,7 @@
 //   w0 [32][1][3][3], b0 [32], then for l = 1..5: wl [32][32][3][3], bl [32],
 //   wh [64][32], bh [64]          (48,672 values)
 #include "common.h"
+#include "windows.h"
 
 #include <math.h>
 #include <algorithm>
@@ -1191,8 +1192,9 @@ constexpr int kWgPart = kWgTiles * 4 * 64;      // raw partial: every lane's acc
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kPastRow = 0x7ffffff0;             // an offset outside every row
-// A buffer descriptor over one row of `bytes` (none: every load returns zero).
+constexpr int kPastRow = 0x7ffffff0;             // an offset outside every descriptor here
+// A buffer descriptor over `bytes` of a row (none: every load returns zero).  It covers a
+// strip's columns and not the row, whose bytes 32 bits do not count up to the widest image.
 __device__ inline __amdgpu_buffer_rsrc_t row_rsrc(const void *row, int bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(row), 0, bytes, 0x00027000);
 }
@@ -1214,14 +1216,15 @@ __global__ __launch_bounds__(64 * kWgWaves, 1) void cnn_conv_bwd_weight_kernel(
         const int n = (int)(it / ((long)strips * bands)), sx = (int)(it % strips) * 32;
         const int ya = (int)(it / strips % bands) * kWgRows * kWgWaves + wave * kWgRows;
         const int yb = min(ya + kWgRows, H);
+        const Columns cols = strip_columns(W, sx, 1);
         auto row_of = [&](const T *base, int y) {
-            return row_rsrc(base + ((size_t)n * H + (y >= 0 && y < H ? y : 0)) * W * kC,
-                            y >= 0 && y < H ? W * PB : 0);
+            return row_rsrc(base + (((size_t)n * H + (y >= 0 && y < H ? y : 0)) * W + cols.first) * kC,
+                            y >= 0 && y < H ? cols.n * PB : 0);
         };
         if constexpr (sizeof(T) == 2) {
             // pixels sx + 8 kq - 1 .. + 8 of the lane's channel pair; columns outside
             // the row (-1 or past W) are outside the descriptor and read as zero
-            const int v0 = (sx + 8 * kq) * PB + 4 * i16;
+            const int v0 = (sx - cols.first + 8 * kq) * PB + 4 * i16;
             const int vm = sx + 8 * kq > 0 ? v0 - PB : kPastRow;
             // rows in flight: two ahead (a row's products take less than the latency)
             unsigned rxs[2][10], rds[2][8];
@@ -1292,7 +1295,7 @@ __global__ __launch_bounds__(64 * kWgWaves, 1) void cnn_conv_bwd_weight_kernel(
                 const __amdgpu_buffer_rsrc_t rx[3] = {row_of(x, y - 1), row_of(x, y), row_of(x, y + 1)};
 #pragma unroll 2
                 for (int s = 0; s < 8; ++s) {
-                    const int px = sx + 4 * s + kq, v = px * PB + 8 * i16;
+                    const int px = sx + 4 * s + kq, v = (px - cols.first) * PB + 8 * i16;
                     auto load = [&](const __amdgpu_buffer_rsrc_t &r, int off) {
                         const auto w = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
                         return make_float2(__uint_as_float(w[0]), __uint_as_float(w[1]));
@@ -1365,25 +1368,26 @@ __global__ __launch_bounds__(256) void cnn_conv0_bwd_weight_kernel(const float *
     const long gw = (long)blockIdx.x * 4 + wave, rows = (long)H * B;
     for (long row = gw; row < rows; row += (long)gridDim.x * 4) {
         const int y = (int)(row % H), yy = y + dy;
-        const auto rd = row_rsrc(dz + (size_t)row * W * kC, W * PB);
         const bool yok = i16 < 9 && yy >= 0 && yy < H;
         const float *xr = x0 + (size_t)(row - y + (yok ? yy : y)) * W;
-        for (int s0 = 0; s0 < W; s0 += 32)
+        for (int s0 = 0; s0 < W; s0 += kStripCols) {
+            const auto rd = row_rsrc(dz + ((size_t)row * W + s0) * kC, strip_columns(W, s0, 0).n * PB);
 #pragma unroll
-        for (int s = s0; s < s0 + 32; s += 4) {     // past W dz reads as zero
-            const int px = s + kq, xx = px + dx;
-            const float xl = xr[min(max(xx, 0), W - 1)];
-            const float b = i16 == 9 ? 1.f : (yok && xx >= 0 && xx < W ? xl : 0.f);
-            float2 d;
-            if constexpr (sizeof(T) == 2) {
-                const unsigned w = __builtin_amdgcn_raw_buffer_load_b32(rd, px * PB + 4 * i16, 0, 0);
-                d = make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
-            } else {
-                const auto w = __builtin_amdgcn_raw_buffer_load_b64(rd, px * PB + 8 * i16, 0, 0);
-                d = make_float2(__uint_as_float(w[0]), __uint_as_float(w[1]));
+            for (int s = 0; s < kStripCols; s += 4) {   // past W dz reads as zero
+                const int px = s + kq, xx = s0 + px + dx;
+                const float xl = xr[min(max(xx, 0), W - 1)];
+                const float b = i16 == 9 ? 1.f : (yok && xx >= 0 && xx < W ? xl : 0.f);
+                float2 d;
+                if constexpr (sizeof(T) == 2) {
+                    const unsigned w = __builtin_amdgcn_raw_buffer_load_b32(rd, px * PB + 4 * i16, 0, 0);
+                    d = make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
+                } else {
+                    const auto w = __builtin_amdgcn_raw_buffer_load_b64(rd, px * PB + 8 * i16, 0, 0);
+                    d = make_float2(__uint_as_float(w[0]), __uint_as_float(w[1]));
+                }
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.x, b, acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.y, b, acc[1], 0, 0, 0);
             }
-            acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.x, b, acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.y, b, acc[1], 0, 0, 0);
         }
     }
     __shared__ float red[4][kW0Part];

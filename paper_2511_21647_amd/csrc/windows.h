@@ -27,4 +27,17 @@ constexpr Window mot_window(int s, int F, int f, int nz, int nu, int z0, int row
     return {((size_t)s * F + f) * frame + (size_t)z0 * nu, rows * nu * 8};
 }
 
+// Network training: the columns [first, first + n) of a row of W pixels that a strip of 32
+// from column sx on reads with `halo` columns on either side.
+constexpr int kStripCols = 32;
+
+struct Columns {
+    int first, n;
+};
+
+constexpr Columns strip_columns(int W, int sx, int halo) {
+    const int first = sx > halo ? sx - halo : 0, end = sx + kStripCols + halo;
+    return {first, (end < W ? end : W) - first};
+}
+
 }  // namespace ulm

@@ -44,6 +44,39 @@ int main() {
 }
 """
 
+TRAINING = r"""
+#include "windows.h"
+#include <cstdio>
+#include <cstdlib>
+using namespace ulm;
+// the first and last strips of a row of W pixels of 64 bytes (BF16) or 128 (FP32)
+static void check(int W, int halo) {
+    const int strips = (W + kStripCols - 1) / kStripCols;
+    for (int s = 0; s < strips; ++s) {
+        if (s == 3 && strips > 8) s = strips - 4;
+        const int sx = s * kStripCols;
+        const Columns c = strip_columns(W, sx, halo);
+        bool ok = c.first >= 0 && c.n > 0 && c.first + c.n <= W;
+        for (int px = sx - halo; px < sx + kStripCols + halo; ++px)
+            for (int pb = 64; pb <= 128; pb *= 2) {
+                if (px < 0) { ok = ok && c.n * pb < 0x7ffffff0; continue; }     // the kernels' kPastRow
+                const long long off = (long long)(px - c.first) * pb;
+                const bool inside = off >= 0 && off + pb <= (long long)c.n * pb;
+                ok = ok && off >= 0 && off < (1ll << 31) && inside == (px < W);
+            }
+        if (!ok) { std::printf("strip %d of %d, halo %d\n", s, W, halo); std::exit(1); }
+    }
+}
+int main() {
+    const int widths[] = {1, 31, 32, 33, 64, 65, 274, (1 << 24) + 33, (1 << 25) - 1};
+    for (int W : widths) {
+        check(W, 0);
+        check(W, 1);
+    }
+    return 0;
+}
+"""
+
 
 def _run(tmp_path, source):
     src, exe = tmp_path / "check.cpp", tmp_path / "check"
@@ -55,6 +88,6 @@ def _run(tmp_path, source):
     assert r.returncode == 0, r.stdout
 
 
-@pytest.mark.parametrize("source", [MOTION], ids=["motion"])
+@pytest.mark.parametrize("source", [MOTION, TRAINING], ids=["motion", "training"])
 def test_windows(tmp_path, source):
     _run(tmp_path, source)
