@@ -39,7 +39,7 @@ struct SepArgs {
     unsigned pmag[kSepMaxPass];             // floor(2^32 / p) + 1 for the pass's p (0 when p = 1)
     int n_tw;                               // twiddle entries (all passes)
     const float2 *twt;                      // [n_tw + 21] twiddles, then the radix roots
-    const float2 *twf;                      // [F] exp(-2 pi i n / F), for the two-pass form
+    const float2 *twf;                      // [2][F] exp(-2 pi i n / F), and over F, for the two-pass form
     int lo[kSepMaxSub], hi[kSepMaxSub];     // |k| range of each subset
 };
 
@@ -89,8 +89,10 @@ __device__ inline void sep_dft(float2 (&u)[R], const float2 *wr)
         constexpr float s2 = 0.587785252292473129168706f;     // sin(4 pi / 5)
         const float2 t1 = add(u[1], u[4]), t2 = add(u[2], u[3]);
         const float2 t3 = sub(u[1], u[4]), t4 = sub(u[2], u[3]);
-        const float2 a1 = add(u[0], add(scl(t1, c1), scl(t2, c2)));
-        const float2 a2 = add(u[0], add(scl(t1, c2), scl(t2, c1)));
+        auto even = [&](float p, float q) {
+            return make_float2(fmaf(t2.x, q, fmaf(t1.x, p, u[0].x)), fmaf(t2.y, q, fmaf(t1.y, p, u[0].y)));
+        };
+        const float2 a1 = even(c1, c2), a2 = even(c2, c1);
         const float2 b1 = mul_mi<INV>(add(scl(t3, s1), scl(t4, s2)));
         const float2 b2 = mul_mi<INV>(sub(scl(t3, s2), scl(t4, s1)));
         u[0] = add(u[0], add(t1, t2));
@@ -234,7 +236,7 @@ __global__ __launch_bounds__(kSepThreads) void sep_kernel(const float2 *__restri
 }
 
 // ---------------------------------------------------------------- two-pass form
-// F = R1 R2 with both factors among kSepRadices: the transform is two passes whose
+// F = R1 R2 with both factors among sep_is_radix: the transform is two passes whose
 // butterflies stay in registers.  With n = i + R2 q and k = m1 + R1 m2,
 //   X[k] = sum_i w_F^{i m1} [sum_q x[n] w_R1^{q m1}] w_R2^{i m2},
 // so thread (i, pixel) takes the R1 frames i + R2 q straight from memory, thread
@@ -243,11 +245,15 @@ __global__ __launch_bounds__(kSepThreads) void sep_kernel(const float2 *__restri
 // inverse in the registers that hold them, one exchange through LDS, the twiddles and
 // the R1-point inverse, and the frames straight to memory.  One LDS exchange a
 // transform (the general kernel: one a radix and the staging).
-// Bound by the stores: six subsets of 2 x 300 frames of 68500 pixels 1189 -> 552 us, of
+// Bound by the stores: six subsets of 2 x 300 frames of 68500 pixels 1189 -> 546 us, of
 // which the loads and stores alone take 560 and all but the stores 380 (one or two
 // work-groups a CU overlap the two; consecutive work-groups on one XCD, whose L2 joins
 // the lines they share, 946 us without).  20 frames of 64 x 64 pixels 25 -> 11 us, 512 of
 // 150 x 200 1066 -> 450 us.
+// Rounding: the error against 64 bits is 0.90 of the general kernel's form on average over
+// the frame counts, at 12 frames 1.03 and elsewhere at most 1.01 (300: 1.32e-7 against
+// 1.49e-7), because the coprime factors of a radix have no twiddles, and 1 / F comes with
+// the inverse's twiddles instead of as a rounding of its own.
 
 // cos and sin of 2 pi q / R at compile time (Taylor series about the nearest octant's
 // multiple, in double)
@@ -275,18 +281,57 @@ constexpr double sep_sin(int q, int R) {
     return sep_series(2.0 * kSepPi * q / R, true);
 }
 
+// cos and sin of 2 pi q / R, what their rounding leaves over in the l arrays.
 template <int R> struct SepRoots {
-    float c[R], s[R];
-    constexpr SepRoots() : c(), s() {
+    float c[R], s[R], cl[R], sl[R];
+    constexpr SepRoots() : c(), s(), cl(), sl() {
         for (int q = 0; q < R; ++q) {
             c[q] = (float)sep_cos(q, R);
             s[q] = (float)sep_sin(q, R);
+            cl[q] = (float)(sep_cos(q, R) - (double)c[q]);
+            sl[q] = (float)(sep_sin(q, R) - (double)s[q]);
         }
     }
 };
 
-// In-place R-point DFT in registers, as sep_dft; R = A B by A-point and B-point DFTs.
-template <int R, bool INV>
+// z (c - i s), or z (c + i s) for INV; c and s one float each, or the sum of two.
+template <bool INV>
+__device__ inline float2 sep_turn(float2 z, float c, float s)
+{
+    const float t = INV ? -s : s;
+    return make_float2(fmaf(z.x, c, z.y * t), fmaf(z.y, c, -z.x * t));
+}
+template <bool INV>
+__device__ inline float2 sep_turn(float2 z, float c, float s, float cl, float sl)
+{
+    const float t = INV ? -s : s, tl = INV ? -sl : sl;
+    return make_float2(fmaf(z.x, c, fmaf(z.y, t, fmaf(z.x, cl, z.y * tl))),
+                       fmaf(z.y, c, fmaf(-z.x, t, fmaf(z.y, cl, -z.x * tl))));
+}
+
+// The smallest factor A of R that has none in common with R / A (R if there is none).
+constexpr int sep_coprime(int R) {
+    for (int a = 2; a < R; ++a) {
+        int x = a, y = R / a;
+        while (y != 0) {
+            const int t = x % y;
+            x = y;
+            y = t;
+        }
+        if (R % a == 0 && x == 1) return a;
+    }
+    return R;
+}
+
+// In-place R-point DFT in registers, as sep_dft.  R = A B with coprime factors goes by
+// the prime-factor algorithm (Good and Thomas): with n = (B n1 + A n2) mod R,
+//   X[k] = sum_n1 w_A^{n1 k} sum_n2 w_B^{n2 k} x[n],
+// A-point and B-point DFTs without twiddles between them.  Powers of one prime have
+// twiddles between the two: 9 and 16 as a pass's whole radix of two floats, as one float's
+// rounding makes the transform less exact than radix by radix there (81, 256 and 512 frames
+// by 3-4%) and not elsewhere (324 by 1%), and in 27 and 18 two take 405 and 486 frames past
+// 128 registers (382 -> 444 and 435 -> 515 us).
+template <int R, bool INV, bool TOP = true>
 __device__ inline void sep_reg_dft(float2 (&u)[R])
 {
     if constexpr (R <= 5) {
@@ -318,8 +363,24 @@ __device__ inline void sep_reg_dft(float2 (&u)[R])
         }
 #pragma unroll
         for (int q = 0; q < R; ++q) u[q] = o[q];
+    } else if constexpr (sep_coprime(R) < R) {
+        constexpr int A = sep_coprime(R), B = R / A;
+        float2 v[A][B];
+#pragma unroll
+        for (int n2 = 0; n2 < B; ++n2) {
+            float2 x[A];
+#pragma unroll
+            for (int n1 = 0; n1 < A; ++n1) x[n1] = u[(B * n1 + A * n2) % R];
+            sep_reg_dft<A, INV, TOP>(x);
+#pragma unroll
+            for (int k = 0; k < A; ++k) v[k][n2] = x[k];
+        }
+#pragma unroll
+        for (int k = 0; k < A; ++k) sep_reg_dft<B, INV, TOP>(v[k]);
+#pragma unroll
+        for (int k = 0; k < R; ++k) u[k] = v[k % A][k % B];
     } else {
-        constexpr int A = R % 4 == 0 ? 4 : (R % 5 == 0 ? 5 : (R % 3 == 0 ? 3 : (R % 7 == 0 ? 7 : 2)));
+        constexpr int A = R % 4 == 0 ? 4 : (R % 5 == 0 ? 5 : 3);
         constexpr int B = R / A;
         constexpr SepRoots<R> w;
         float2 v[A][B];
@@ -328,18 +389,19 @@ __device__ inline void sep_reg_dft(float2 (&u)[R])
             float2 x[A];
 #pragma unroll
             for (int q = 0; q < A; ++q) x[q] = u[i + B * q];
-            sep_reg_dft<A, INV>(x);
+            sep_reg_dft<A, INV, false>(x);
 #pragma unroll
             for (int m = 0; m < A; ++m) {
-                const float c = w.c[i * m], s = w.s[i * m];      // exp(-+ 2 pi i (i m) / R)
-                v[m][i] = i * m == 0 ? x[m]
-                          : INV ? make_float2(fmaf(x[m].x, c, -x[m].y * s), fmaf(x[m].x, s, x[m].y * c))
-                                : make_float2(fmaf(x[m].x, c, x[m].y * s), fmaf(-x[m].x, s, x[m].y * c));
+                // exp(-+ 2 pi i (i m) / R)
+                const int j = i * m;
+                if (j == 0) v[m][i] = x[m];
+                else if (TOP && (R == 9 || R == 16)) v[m][i] = sep_turn<INV>(x[m], w.c[j], w.s[j], w.cl[j], w.sl[j]);
+                else v[m][i] = sep_turn<INV>(x[m], w.c[j], w.s[j]);
             }
         }
 #pragma unroll
         for (int m = 0; m < A; ++m) {
-            sep_reg_dft<B, INV>(v[m]);
+            sep_reg_dft<B, INV, false>(v[m]);
 #pragma unroll
             for (int m2 = 0; m2 < B; ++m2) u[m + A * m2] = v[m][m2];
         }
@@ -375,8 +437,12 @@ __global__ __launch_bounds__(sep_threads(R2)) void sep_two_kernel(
     const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float2 *>(P + at), 0, F * row, 0x00027000);
 
-    __shared__ float2 tw[F];                      // exp(-2 pi i n / F)
-    for (int e = threadIdx.x; e < F; e += sep_threads(R2)) tw[e] = g.twf[e];
+    // exp(-2 pi i n / F), and over F for the inverses (side by side: one address)
+    __shared__ float2 tw[F][2];
+    for (int e = threadIdx.x; e < F; e += sep_threads(R2)) {
+        tw[e][0] = g.twf[e];
+        tw[e][1] = g.twf[F + e];
+    }
     lds_barrier();
     if (first) {
         float2 u[R1];
@@ -387,7 +453,7 @@ __global__ __launch_bounds__(sep_threads(R2)) void sep_two_kernel(
         }
         sep_reg_dft<R1, false>(u);
 #pragma unroll
-        for (int m = 0; m < R1; ++m) ex[m][i * kPix + px] = m == 0 ? u[m] : cmulf(u[m], tw[i * m]);
+        for (int m = 0; m < R1; ++m) ex[m][i * kPix + px] = m == 0 ? u[m] : cmulf(u[m], tw[i * m][0]);
     }
     lds_barrier();
     float2 X[R2];
@@ -396,7 +462,8 @@ __global__ __launch_bounds__(sep_threads(R2)) void sep_two_kernel(
         for (int n = 0; n < R2; ++n) X[n] = ex[i][n * kPix + px];
         sep_reg_dft<R2, false>(X);
     }
-    const float scale = 1.0f / (float)F;
+    // 1 / F for the terms without a twiddle, as the sum of two floats
+    constexpr float s_hi = (float)(1.0 / F), s_lo = (float)(1.0 / F - (double)s_hi);
     const size_t sub_stride = (size_t)g.planes * F * g.npix;
     for (int s = 0; s < g.n_sub; ++s) {
         // bins [k0, k0 + n): lo.. up, or F - hi + 1.. down
@@ -420,7 +487,8 @@ __global__ __launch_bounds__(sep_threads(R2)) void sep_two_kernel(
 #pragma unroll
             for (int m = 0; m < R1; ++m) {
                 const float2 v = ex[m][i * kPix + px];
-                u[m] = m == 0 ? v : cmulf_conj(v, tw[i * m]);
+                u[m] = m == 0 ? make_float2(fmaf(v.x, s_hi, v.x * s_lo), fmaf(v.y, s_hi, v.y * s_lo))
+                              : cmulf_conj(v, tw[i * m][1]);
             }
             sep_reg_dft<R1, true>(u);
             const __amdgpu_buffer_rsrc_t dst =
@@ -428,7 +496,7 @@ __global__ __launch_bounds__(sep_threads(R2)) void sep_two_kernel(
 #pragma unroll
             for (int q = 0; q < R1; ++q)
                 __builtin_amdgcn_raw_buffer_store_b64(
-                    __builtin_bit_cast(u32x2, f32x2{u[q].x * scale, u[q].y * scale}), dst, off, R2 * q * row, 0);
+                    __builtin_bit_cast(u32x2, f32x2{u[q].x, u[q].y}), dst, off, R2 * q * row, 0);
         }
     }
 }
@@ -486,8 +554,8 @@ bool separate_supported(int F) {
 // The kernel's table for F frames: tw[tw_off[s] + k R + q] = exp(-2 pi i q k /
 // (p R)) for every pass s (radix R, p = product of the earlier radices), then
 // the roots exp(-2 pi i q / R) of R = 2, 3, 4, 5, 7 (2 + 3 + 4 + 5 + 7 = 21
-// entries), then exp(-2 pi i n / F) of n < F for the two-pass form; FP64, rounded to
-// FP32.  Empty if F is not supported.
+// entries), then for the two-pass form exp(-2 pi i n / F) of n < F, and the same over F;
+// FP64, rounded to FP32.  Empty if F is not supported.
 std::vector<float2> separate_twiddles(int F) {
     SepArgs g;
     if (!separate_supported(F)) return {};
@@ -510,6 +578,10 @@ std::vector<float2> separate_twiddles(int F) {
     for (int r : rad)
         for (int q = 0; q < r; ++q) t[o++] = root(-(double)q / (double)r);
     for (int n = 0; n < F; ++n) t.push_back(root(-(double)n / (double)F));
+    for (int n = 0; n < F; ++n) {
+        const double a = 2.0 * M_PI * (double)n / (double)F;
+        t.push_back(make_float2((float)(std::cos(a) / F), (float)(-std::sin(a) / F)));
+    }
     return t;
 }
 
