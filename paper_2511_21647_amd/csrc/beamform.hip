@@ -161,9 +161,13 @@ __global__ __launch_bounds__(256, 4) void stage2_fir_kernel(
 // the form above (one scalar load and one loop step per tap: 12.4 ms for 2 x 35 slabs
 // of 250 x 274 x 300).  Here a (transmit, slab) costs two LDS reads for its taps
 // (staged once per work-group) and eleven reads of the slice tile for 8 x taps x 4
-// FMAs; the next transmit's tile is in flight during it, and the planes, which nothing
-// reads soon, are stored past the caches.  6.1 ms: 4.6 without the stores of 11.5 GB,
-// about 3.5 of FMAs alone.  Groups of 5 to 12 slabs with 4 or 8 rows per thread and 3 to
+// FMAs; the next transmit's tile is in flight during it.  The planes, which nothing
+// reads soon, are stored past the caches where their rows are whole 128-byte lines (64 x
+// 64 planes, 9 transmits 109 -> 99 us; 250 x 272, 2 transmits 237 -> 160) or the stores
+// come slowly, with more than four transmits (250 x 274, 9 transmits, 20 frames 520 ->
+// 503 us).  Otherwise parts of lines would reach memory one by one, which the L2 joins
+// (250 x 274, one transmit 357 -> 254 us, four 369 -> 350).  6.1 ms: 4.6 without the stores
+// of 11.5 GB, about 3.5 of FMAs alone.  Groups of 5 to 12 slabs with 4 or 8 rows per thread and 3 to
 // 6 waves per SIMD all take 6.1-7.2 ms.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
@@ -191,7 +195,8 @@ __device__ inline void slab_taps(const float2 (*tile)[kFirTileU], const float2 *
         }
 }
 
-template <int SPAN>      // halo rows: the union of the group's tap ranges fits
+// SPAN: halo rows (the union of the group's tap ranges fits); PAST: stores past the caches
+template <int SPAN, bool PAST>
 __global__ __launch_bounds__(256, 3) void stage2_slab_kernel(
     const float2 *__restrict__ S, float2 *__restrict__ P, const float2 *__restrict__ taps,
     const int2 *__restrict__ meta, Geometry g, int max_taps)
@@ -286,9 +291,12 @@ __global__ __launch_bounds__(256, 3) void stage2_slab_kernel(
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int l = l0 + rg * R + r;
-            if (l < g.nz)
-                __builtin_nontemporal_store(f32x2{acc[gb][r].x, acc[gb][r].y},
-                                            reinterpret_cast<f32x2 *>(&dst[(size_t)l * g.nu + u]));
+            if (l >= g.nz) continue;
+            float2 *at = &dst[(size_t)l * g.nu + u];
+            if constexpr (PAST)
+                __builtin_nontemporal_store(f32x2{acc[gb][r].x, acc[gb][r].y}, reinterpret_cast<f32x2 *>(at));
+            else
+                *at = acc[gb][r];
         }
     }
 }
@@ -300,12 +308,14 @@ hipError_t launch_stage2(const ulm_ctx *ctx, const float2 *slices, float2 *proj,
     const size_t n_wg = (size_t)2 * g.n_frames * cdiv(g.nu, kFirTileU) * cdiv(g.nz, G == kSlabGroup ? 8 * kSlabRows : kFirTileZ) *
                         cdiv(g.n_blocks, G);
     if (n_wg > (size_t)INT32_MAX) return hipErrorInvalidConfiguration;
-    if (G == kSlabGroup)
-        hipLaunchKernelGGL(ctx->tab.fir_span <= kSlabSpan ? stage2_slab_kernel<kSlabSpan>
-                                                          : stage2_slab_kernel<kSlabMaxSpan>,
+    if (G == kSlabGroup) {
+        const bool narrow = ctx->tab.fir_span <= kSlabSpan, past = g.nu % 16 == 0 || g.n_angles > 4;
+        hipLaunchKernelGGL(narrow ? (past ? stage2_slab_kernel<kSlabSpan, true> : stage2_slab_kernel<kSlabSpan, false>)
+                                  : (past ? stage2_slab_kernel<kSlabMaxSpan, true>
+                                          : stage2_slab_kernel<kSlabMaxSpan, false>),
                            dim3((unsigned)n_wg), dim3(256), 0, st, slices, proj, ctx->tab.taps,
                            ctx->tab.tap_meta, g, ctx->tab.n_taps);
-    else if (G == kFirGroup)
+    } else if (G == kFirGroup)
         hipLaunchKernelGGL(stage2_fir_kernel<kFirGroup>, dim3((unsigned)n_wg), dim3(256), 0, st,
                            slices, proj, ctx->tab.taps, ctx->tab.tap_meta, g, ctx->tab.n_taps);
     else
