@@ -7,8 +7,8 @@
 // slabs per orientation, XZ records of slab b pair only with YZ records whose
 // y lies in slab b, and their x must lie in the YZ record's slab.
 //
-//   pair_bounds_kernel  record range of every (plane, frame) in the sorted list
-//   pair_order_kernel   whether each range is in row order
+//   pair_bounds_kernel  record range of every (plane, frame) in the sorted list, and
+//                       whether it is in row order
 //   pair_best_kernel    every record's best candidate (one thread per record)
 //   pair_count_kernel   mutual pairs per (frame, XZ plane)
 //   launch_scan         their offsets, XZ planes fastest (the localisers' scan)
@@ -23,7 +23,7 @@
 namespace ulm {
 
 // Record range [2 key], [2 key + 1] of a (plane, frame); the top bit of the second
-// word marks a range whose records are not in row order (see pair_order_kernel).
+// word marks a range whose records are not in row order (see pair_bounds_kernel).
 constexpr int kPairUnordered = INT32_MIN;
 
 struct PairArgs {
@@ -44,40 +44,44 @@ __device__ inline int slab_of(float pix, int per) {
 
 __device__ inline int key_of(const ulm_loc_t &r, int F) { return r.plane * F + r.frame; }
 
-__global__ void pair_bounds_kernel(const ulm_loc_t *__restrict__ locs, const int *__restrict__ count,
-                                   int capacity, int nkeys, int F, int *__restrict__ bounds)
+// The record range of every (plane, frame), by bisection, and whether it is in row order:
+// a record's candidates lie within one pixel axially, so in a range that is sorted by row
+// (as the localisers write it), with every z within half a pixel of its row, they are a
+// short run.  T threads per key walk the range: a work-group where there are few keys, so
+// that a long range is short work, and 16 lanes where there are many, so that one round of
+// waves takes them all.  (As a pass of its own over the list the order took another
+// launch, 2 of the 30 us that pairing a short list takes.)
+constexpr int pair_threads(int T) { return T > 256 ? T : 256; }
+template <int T>
+__global__ __launch_bounds__(pair_threads(T)) void pair_bounds_kernel(PairArgs a, int nkeys)
 {
-    const int key = blockIdx.x * blockDim.x + threadIdx.x;
-    if (key >= nkeys) return;
-    const int n = min(*count, capacity);
-    auto lower = [&](int k) {          // first record with key >= k
-        int lo = 0, hi = n;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (key_of(locs[mid], F) < k) lo = mid + 1; else hi = mid;
-        }
-        return lo;
-    };
-    bounds[2 * key] = lower(key);
-    bounds[2 * key + 1] = lower(key + 1);
-}
-
-// A record's candidates lie within one pixel axially, so in a range that is sorted by
-// row (as the localisers write it), with every z within half a pixel of its row, they
-// are a short run.  One pass over the list marks the ranges where that does not hold.
-__global__ __launch_bounds__(256) void pair_order_kernel(PairArgs a, int nkeys)
-{
+    const int key = blockIdx.x * (pair_threads(T) / T) + threadIdx.x / T, t = threadIdx.x % T;
     const int n = min(*a.count, a.capacity);
-    for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
-        const int4 w = *reinterpret_cast<const int4 *>(&a.locs[r]);
-        const int key = w.x * a.F + w.y;
-        if (key < 0 || key >= nkeys) continue;
-        bool bad = !(fabsf(a.locs[r].z - (float)w.z) <= 0.5f) || abs(w.z) > (1 << 20);
-        if (r + 1 < n) {
-            const int4 x = *reinterpret_cast<const int4 *>(&a.locs[r + 1]);
-            bad |= x.x * a.F + x.y == key && x.z < w.z;
+    // lane q of a pair: the first record with a key of at least key + q
+    const int want = key + (t & 1);
+    int first = 0, last = n;
+    while (first < last) {
+        const int mid = (first + last) >> 1;
+        if (key_of(a.locs[mid], a.F) < want) first = mid + 1; else last = mid;
+    }
+    constexpr int W = T < 64 ? T : 64;
+    const int lo = __shfl(first, 0, W), hi = __shfl(first, 1, W);
+    bool bad = false;
+    if (key < nkeys)
+#pragma unroll 4
+        for (int r = lo + t; r < hi; r += T) {
+            const int iz = a.locs[r].iz;
+            bad |= !(fabsf(a.locs[r].z - (float)iz) <= 0.5f) || abs(iz) > (1 << 20);
+            bad |= a.locs[min(r + 1, hi - 1)].iz < iz;
         }
-        if (bad) atomicOr(&a.bounds[2 * key + 1], kPairUnordered);
+    if constexpr (T > 64) {
+        bad = __syncthreads_or(bad);
+    } else {
+        for (int o = T / 2; o > 0; o >>= 1) bad |= __shfl_xor((int)bad, o) != 0;
+    }
+    if (key < nkeys && t == 0) {
+        a.bounds[2 * key] = lo;
+        a.bounds[2 * key + 1] = bad ? hi | kPairUnordered : hi;
     }
 }
 
@@ -228,8 +232,6 @@ hipError_t launch_pairing(const ulm_ctx *ctx, const ulm_loc_t *locs, const int *
     int *cnt = (int *)((char *)best + a256(sizeof(int) * (size_t)std::max(capacity, 1)));
     int *off = (int *)((char *)cnt + a256(sizeof(int) * (size_t)F * B));
     const int nkeys = planes * F;
-    hipLaunchKernelGGL(pair_bounds_kernel, dim3(cdiv(nkeys, 256)), dim3(256), 0, st, locs, count,
-                       capacity, nkeys, F, bounds);
     PairArgs a;
     a.locs = locs;
     a.count = count;
@@ -243,7 +245,9 @@ hipError_t launch_pairing(const ulm_ctx *ctx, const ulm_loc_t *locs, const int *
     a.off = off;
     // eight work-groups per CU walk the list
     const int wgs = std::max(1, std::min(2048, cdiv(capacity, 256)));
-    hipLaunchKernelGGL(pair_order_kernel, dim3(wgs), dim3(256), 0, st, a, nkeys);
+    const int T = nkeys <= 256 ? 1024 : (nkeys <= 2048 ? 256 : 16);
+    hipLaunchKernelGGL(T == 1024 ? pair_bounds_kernel<1024> : (T == 256 ? pair_bounds_kernel<256> : pair_bounds_kernel<16>),
+                       dim3(cdiv(nkeys, pair_threads(T) / T)), dim3(pair_threads(T)), 0, st, a, nkeys);
     hipLaunchKernelGGL(pair_best_kernel, dim3(wgs), dim3(256), 0, st, a, nkeys);
     hipLaunchKernelGGL(pair_count_kernel, dim3(F, B), dim3(256), 0, st, a);
     hipError_t e = launch_scan(cnt, off, F * B, out_count, st);
