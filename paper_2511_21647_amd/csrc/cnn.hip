@@ -1180,10 +1180,11 @@ __global__ __launch_bounds__(64 * kHtWaves, 2) void cnn_head_train_kernel(
 // the operands of the even and of the odd channels: no LDS, no transpose.  A row of
 // x is loaded once and held as the operands of the three column taps while it
 // serves the three row taps.  The bias is one more product, against ones.
-// A wave takes 8 rows of a 32-pixel strip at a time; its 38 accumulators (152
-// registers) stay over all of a work-group's strips, and the four waves are summed
-// in LDS at the end, so a work-group writes one partial.  One wave per SIMD: the 38
-// products of a row are independent, and the next row's loads are in flight.
+// A wave takes `band` rows (8, or fewer where that leaves CUs without one: a wave's rows
+// are a serial chain, 6 us each in FP32) of a 32-pixel strip at a time; its 38
+// accumulators (152 registers) stay over all of a work-group's strips, and the four waves
+// are summed in LDS at the end, so a work-group writes one partial.  One wave per SIMD: the
+// 38 products of a row are independent, and the next row's loads are in flight.
 // Bound by the matrix products (16 cycles each).  With one FMA per LDS operand it
 // took 1.38 ms a layer on 16 images of 250 x 274.
 constexpr int kWgRows = 8, kWgWaves = 4, kWgTiles = 38;
@@ -1201,7 +1202,7 @@ __device__ inline __amdgpu_buffer_rsrc_t row_rsrc(const void *row, int bytes) {
 
 template <typename T>
 __global__ __launch_bounds__(64 * kWgWaves, 1) void cnn_conv_bwd_weight_kernel(
-    const T *__restrict__ x, const T *__restrict__ dz, float *__restrict__ part, int H, int W, int B)
+    const T *__restrict__ x, const T *__restrict__ dz, float *__restrict__ part, int H, int W, int B, int band)
 {
     __shared__ float red[2][kWgPart];
     const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
@@ -1209,13 +1210,13 @@ __global__ __launch_bounds__(64 * kWgWaves, 1) void cnn_conv_bwd_weight_kernel(
     f32x4 acc[kWgTiles];        // (tap, o parity, c parity), then the bias of each o parity
 #pragma unroll
     for (int i = 0; i < kWgTiles; ++i) acc[i] = f32x4{};
-    const int strips = cdiv(W, 32), bands = cdiv(H, kWgRows * kWgWaves);
+    const int strips = cdiv(W, 32), bands = cdiv(H, band * kWgWaves);
     const long items = (long)strips * bands * B;
     constexpr int PB = kC * (int)sizeof(T);                 // bytes per pixel
     for (long it = blockIdx.x; it < items; it += gridDim.x) {
         const int n = (int)(it / ((long)strips * bands)), sx = (int)(it % strips) * 32;
-        const int ya = (int)(it / strips % bands) * kWgRows * kWgWaves + wave * kWgRows;
-        const int yb = min(ya + kWgRows, H);
+        const int ya = ((int)(it / strips % bands) * kWgWaves + wave) * band;
+        const int yb = min(ya + band, H);
         const Columns cols = strip_columns(W, sx, 1);
         auto row_of = [&](const T *base, int y) {
             return row_rsrc(base + (((size_t)n * H + (y >= 0 && y < H ? y : 0)) * W + cols.first) * kC,
@@ -1352,25 +1353,29 @@ __global__ __launch_bounds__(64 * kWgWaves, 1) void cnn_conv_bwd_weight_kernel(
 // Layer-0 weight and bias gradients, dw0[o][tap] = sum_p dz[p][o] x0[p + tap], on
 // v_mfma_f32_16x16x4f32 (x0 is FP32): M = 16 output channels, N = the nine taps and,
 // as a tenth column, ones for the bias, K = 4 pixels of a row.  Each wave takes rows
-// in turn.  Bound by HBM (dz is read once).
+// in turn, or where there are few, segments of `seg` columns (whole strips) of them.
+// Bound by HBM (dz is read once).
 constexpr int kW0Part = 2 * 4 * 64;
 template <typename T>
 __global__ __launch_bounds__(256) void cnn_conv0_bwd_weight_kernel(const float *__restrict__ x0,
                                                                    const T *__restrict__ dz,
                                                                    float *__restrict__ part, int H,
-                                                                   int W, int B)
+                                                                   int W, int B, int seg)
 {
     const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // rows are uniform in a wave
     const int dy = i16 < 9 ? i16 / 3 - 1 : 0, dx = i16 < 9 ? i16 % 3 - 1 : 0;
     constexpr int PB = kC * (int)sizeof(T);
     f32x4 acc[2] = {{}, {}};
-    const long gw = (long)blockIdx.x * 4 + wave, rows = (long)H * B;
-    for (long row = gw; row < rows; row += (long)gridDim.x * 4) {
+    const int segs = cdiv(W, seg);
+    const long gw = (long)blockIdx.x * 4 + wave, items = (long)H * B * segs;
+    for (long it = gw; it < items; it += (long)gridDim.x * 4) {
+        const long row = it / segs;
+        const int sa = (int)(it % segs) * seg, sb = min(sa + seg, W);
         const int y = (int)(row % H), yy = y + dy;
         const bool yok = i16 < 9 && yy >= 0 && yy < H;
         const float *xr = x0 + (size_t)(row - y + (yok ? yy : y)) * W;
-        for (int s0 = 0; s0 < W; s0 += kStripCols) {
+        for (int s0 = sa; s0 < sb; s0 += kStripCols) {
             const auto rd = row_rsrc(dz + ((size_t)row * W + s0) * kC, strip_columns(W, s0, 0).n * PB);
 #pragma unroll
             for (int s = 0; s < kStripCols; s += 4) {   // past W dz reads as zero
@@ -1617,13 +1622,19 @@ static hipError_t gradients_t(const float *params, const float *x0, const float 
     hipLaunchKernelGGL(cnn_reduce_kernel<kReduceHead>, dim3(kHtPart / 64), dim3(1024), 0, st, part,
                        gh * kHtWaves, kHtPart, grad + off_wh());
     // conv layers 5..1: weight gradient, then the data gradient through the mask below
-    const long items = (long)cdiv(W, 32) * cdiv(H, kWgRows * kWgWaves) * B;
-    const int gw = (int)std::min((long)kMaxPartials, items);
+    auto conv_items = [&](int band) { return (long)cdiv(W, 32) * cdiv(H, band * kWgWaves) * B; };
+    // FP32's rows are long enough to fill every CU for; BF16's, two in flight, are worth
+    // less than the partials that more work-groups leave (64 of 16 x 16 178 us, with four
+    // times the work-groups 184; one of 64 x 64 in FP32 617 -> 350 us, in BF16 174 -> 160)
+    const int fill = sizeof(T) == 2 ? kMaxPartials / 4 : kMaxPartials;
+    int band = kWgRows;
+    while (band > 1 && conv_items(band) < fill) band /= 2;
+    const int gw = (int)std::min((long)kMaxPartials, conv_items(band));
     const T *wt = (const T *)(ws + L.wt);
     int cur = 0;
     for (int l = kL - 1; l >= 1; --l) {
         hipLaunchKernelGGL(cnn_conv_bwd_weight_kernel<T>, dim3(gw), dim3(64 * kWgWaves), 0, st, act[l - 1],
-                           dz[cur], part, H, W, B);
+                           dz[cur], part, H, W, B, band);
         hipLaunchKernelGGL(cnn_reduce_kernel<kReduceConv>, dim3(kWgPart / 64), dim3(1024), 0, st, part, gw,
                            kWgPart, grad + off_w(l));
         hipLaunchKernelGGL((cnn_conv_kernel<T, true>), dim3(conv_grid(B, H, W)), dim3(256), 0, st,
@@ -1631,9 +1642,12 @@ static hipError_t gradients_t(const float *params, const float *x0, const float 
                            act[l - 1], dz[cur ^ 1], H, W, B);
         cur ^= 1;
     }
-    const int g0 = (int)std::min((long)kConv0Groups, cdiv((long)H * B, 4L));
+    int seg = cdiv(W, kStripCols) * kStripCols;
+    while (seg > kStripCols && (long)H * B * cdiv(W, seg) < kConv0Groups)
+        seg = cdiv(seg / kStripCols, 2) * kStripCols;
+    const int g0 = (int)std::min((long)kConv0Groups, cdiv((long)H * B * cdiv(W, seg), 4L));
     hipLaunchKernelGGL(cnn_conv0_bwd_weight_kernel<T>, dim3(g0), dim3(256), 0, st, x0, dz[cur], part, H,
-                       W, B);
+                       W, B, seg);
     hipLaunchKernelGGL(cnn_reduce_kernel<kReduceConv0>, dim3(kW0Part / 64), dim3(1024), 0, st, part, g0,
                        kW0Part, grad);
     return hipGetLastError();
