@@ -266,8 +266,10 @@ __device__ inline bool reduce_steps(Reduction<NR, NC> &s, const ReductionArgs &a
                 }
             }
         }
-        // the reflector, by the owner of column k + 1: stored once the step's values are
-        // in (a load waits for the stores issued before it)
+        // the reflector, by the owner of column k + 1, ahead of the loads below (after them its
+        // values would stay in registers across the wait; within 1% either way).  Nothing
+        // reads it before the next plane barrier, which waits for it.  (A lambda because the
+        // compiler spills three times as much of the five-row form with it written in place.)
         auto store_reflector = [&]() {
             if (!owner) return;
 #pragma unroll
