@@ -329,7 +329,7 @@ __device__ inline bool reduce_steps(Reduction<NR, NC> &s, const ReductionArgs &a
                 }
                 break;
             }
-            if (++spins > (1 << 20)) {
+            if (++spins > kMaxPolls) {
                 *a.abort_s = 1;
                 if (lane == 0) atomicOr(a.status, kStatusBarrier);
                 break;

@@ -13,6 +13,9 @@ constexpr int kCoopWaves = kCoopThreads / 64;
 constexpr int kCoopRows = 8;     // rows per lane of a column at most: F <= 512
 constexpr int kPoints = 16;      // multisection points per eigenvalue and round
 constexpr int kGroups = 64 / kPoints;   // eigenvalues per wave at a time
+// Polls before a wait gives up and flags the status word, some seconds: far beyond what a
+// work-group can be late for by another kernel on its CU, and far below a hang's limits.
+constexpr int kMaxPolls = 1 << 23;
 
 __device__ inline double2 cmul2(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
@@ -112,7 +115,7 @@ __device__ inline bool plane_barrier(int *flags, int w, int W, int step, int *ab
         int spins = 0;
         while (load_flag(flags + threadIdx.x, mode) < step) {
             __builtin_amdgcn_s_sleep(1);
-            if (++spins > (1 << 23)) {
+            if (++spins > kMaxPolls) {
                 *abort_s = 1;
                 atomicOr(status, kStatusBarrier);
                 break;
