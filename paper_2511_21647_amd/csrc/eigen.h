@@ -20,7 +20,9 @@ struct EigArgs {
     double *tscr;       // [planes][c][6][F]
     double2 *xscr;      // [planes][c][F]
     double2 *xbuf;      // [planes][2][3][F] published p = tau A v, then columns, by step modulo 3
-                        // (eigen_lds.hip: by step modulo 2, in the first four)
+                        // (eigen_lds.hip: p, [planes][2][F] by step modulo 2)
+    double2 *colbuf;    // eigen_lds.hip: published columns, [planes][2][F] (behind p in the same
+                        // buffer; strided by plane as above, 480 frames took 1.4% longer)
     int *bar;           // [planes][kBarStride] barrier flags and the XCC mask, zero at launch
     int *flag;          // [planes] non-finite input
     int *status;

@@ -118,8 +118,8 @@ __global__ __launch_bounds__(kCoopThreads) void eigen_lds_kernel(EigArgs a)
     double2 *tau = a.tau + (size_t)plane * F;
     double *d = a.d + (size_t)plane * F, *e = a.e + (size_t)plane * F;
     // double-buffered exchange areas (by step parity): p and the next column
-    double2 *pbuf = a.xbuf + (size_t)plane * 6 * F;
-    double2 *cbuf = pbuf + 2 * F;
+    double2 *pbuf = a.xbuf + (size_t)plane * 2 * F;
+    double2 *cbuf = a.colbuf + (size_t)plane * 2 * F;
     int *flags = a.bar + (size_t)plane * kBarStride;
     int nbar = 0;
 

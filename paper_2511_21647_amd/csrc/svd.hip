@@ -1240,6 +1240,7 @@ hipError_t launch_filter(const ulm_ctx *ctx, float2 *proj, double *eigvals_out, 
         a.tscr = (double *)(ws + w.tscratch);
         a.xscr = (double2 *)(ws + w.xscratch);
         a.xbuf = (double2 *)(ws + w.xbuf);
+        a.colbuf = a.xbuf + (size_t)planes * 2 * F;
         a.bar = (int *)(ws + w.bar);
         a.flag = (int *)(ws + w.eflag);
         a.status = status;
