@@ -32,7 +32,6 @@ struct EigArgs {
     int plane0;
 };
 
-int eigen_coop_width(int F, int planes);
 size_t eigen_coop_lds(int F, int c);
 hipError_t launch_eigen_coop(const EigArgs &args, hipStream_t st);
 int eigen_lds_width(int F);

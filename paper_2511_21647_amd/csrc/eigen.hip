@@ -826,20 +826,6 @@ __global__ __launch_bounds__(kCoopThreads, NR <= 6 ? 2 : 1) void eigen_coop_kern
     }
 }
 
-// Columns per wave: all of a small plane's in one work-group; else three where the
-// planes fit the chip at once (one per XCD), so that a step's arithmetic is short,
-// and five where there are more, so that four planes of 300 frames instead of two
-// share an XCD and the planes need fewer rounds.  From 385 frames four, which 32
-// work-groups hold up to the largest size.
-int eigen_coop_columns(int F, int planes) {
-    if (F <= 64) return F <= 20 ? 5 : (F <= 32 ? 8 : 16);
-    return F > 384 ? 4 : (planes <= 8 ? 3 : 5);
-}
-
-int eigen_coop_width(int F, int planes) {
-    return cdiv(F, kCoopWaves * eigen_coop_columns(F, planes));
-}
-
 size_t eigen_coop_lds(int F, int c) {
     if (F > 64 * kCoopRows) return SIZE_MAX;
     // reduction: v and p of every wave, the values read; tail: d, e, (d, e^2) and either every
@@ -855,45 +841,74 @@ static EigKernel eigen_kernel_of(int columns) {
     if constexpr (NR == 1)
         return columns == 5 ? eigen_coop_kernel<1, 5> : (columns == 8 ? eigen_coop_kernel<1, 8> : eigen_coop_kernel<1, 16>);
     else if constexpr (NR > 6) return eigen_coop_kernel<NR, 4>;
-    else return columns == 3 ? eigen_coop_kernel<NR, 3> : eigen_coop_kernel<NR, 5>;
+    else return columns == 3 ? eigen_coop_kernel<NR, 3>
+                             : (columns == 4 ? eigen_coop_kernel<NR, 4> : eigen_coop_kernel<NR, 5>);
+}
+static EigKernel eigen_kernel(int F, int columns) {
+    switch (cdiv(F, 64)) {
+        case 1: return eigen_kernel_of<1>(columns);
+        case 2: return eigen_kernel_of<2>(columns);
+        case 3: return eigen_kernel_of<3>(columns);
+        case 4: return eigen_kernel_of<4>(columns);
+        case 5: return eigen_kernel_of<5>(columns);
+        case 6: return eigen_kernel_of<6>(columns);
+        case 7: return eigen_kernel_of<7>(columns);
+        case 8: return eigen_kernel_of<8>(columns);
+        default: return nullptr;
+    }
 }
 
 // A cooperative launch needs every work-group resident at once, so the planes
 // are solved in groups: as many whole rounds of 8 planes (one per XCD) as fit.
+// Columns per wave: all of a small plane's in one work-group; from 385 frames four, which 32
+// work-groups hold up to the largest size; else 3 to 5, the fewest of those that need the
+// fewest groups at two work-groups a CU, because fewer columns make a step's arithmetic
+// shorter and take fewer registers, and more let more planes share an XCD (a third and
+// fourth work-group a CU lengthen every step as much as they save: 70 planes of 128 frames
+// 1.12 ms with three columns, 1.07 with five).  The filter of 70 planes in ms, by columns 3,
+// 4, 5 (* the choice): 300 frames -, 5.90*, 6.35; 321 frames 9.27, 7.08*, 8.31; 352 frames
+// 9.97, 10.55, 9.04*; 384 frames (one work-group a CU by LDS) 15.1*, 16.6, 20.3 (with
+// registers spilled).  10 planes: 321 frames 1.91*, 2.00, 2.23.
 hipError_t launch_eigen_coop(const EigArgs &args, hipStream_t st) {
-    const unsigned lds = (unsigned)eigen_coop_lds(args.F, args.c);
-    const int nc = eigen_coop_columns(args.F, args.planes);
-    EigKernel k = nullptr;
-    switch (cdiv(args.F, 64)) {
-        case 1: k = eigen_kernel_of<1>(nc); break;
-        case 2: k = eigen_kernel_of<2>(nc); break;
-        case 3: k = eigen_kernel_of<3>(nc); break;
-        case 4: k = eigen_kernel_of<4>(nc); break;
-        case 5: k = eigen_kernel_of<5>(nc); break;
-        case 6: k = eigen_kernel_of<6>(nc); break;
-        case 7: k = eigen_kernel_of<7>(nc); break;
-        case 8: k = eigen_kernel_of<8>(nc); break;
-        default: return hipErrorInvalidValue;
-    }
-    if (args.W == 1) {      // no work-group waits for another: an ordinary launch
-        hipLaunchKernelGGL(k, dim3(8 * cdiv(args.planes - args.plane0, 8)), dim3(kCoopThreads), lds, st, args);
+    const int F = args.F;
+    const unsigned lds = (unsigned)eigen_coop_lds(F, args.c);
+    if (F > 64 * kCoopRows) return hipErrorInvalidValue;
+    if (F <= 64) {      // no work-group waits for another: an ordinary launch
+        EigArgs a = args;
+        a.W = 1;
+        hipLaunchKernelGGL(eigen_kernel(F, F <= 20 ? 5 : (F <= 32 ? 8 : 16)),
+                           dim3(8 * cdiv(a.planes - a.plane0, 8)), dim3(kCoopThreads), lds, st, a);
         return hipGetLastError();
     }
-    int dev = 0, ncu = 0, per_cu = 0;
+    int dev = 0, ncu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)k, kCoopThreads, lds);
     if (e != hipSuccess) return e;
-    const int resident = per_cu * ncu;
-    const int group = resident / (8 * args.W) * 8;           // whole rounds of 8 planes
-    if (group == 0) return hipErrorCooperativeLaunchTooLarge;
+    int W = 0, group = 0, launches = 0;
+    EigKernel k = nullptr;
+    for (int columns = F > 384 ? 4 : 3; columns <= (F > 384 ? 4 : 5); ++columns) {
+        const int w = cdiv(F, kCoopWaves * columns);
+        const EigKernel kc = eigen_kernel(F, columns);
+        int per_cu = 0;
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kc, kCoopThreads, lds);
+        if (e != hipSuccess) return e;
+        // whole rounds of 8 planes, of two work-groups a CU for the choice
+        const int fit = std::min(per_cu, 2) * ncu / (8 * w) * 8;
+        if (fit == 0 || (k && cdiv(args.planes, fit) >= launches)) continue;
+        launches = cdiv(args.planes, fit);
+        W = w;
+        group = per_cu * ncu / (8 * w) * 8;
+        k = kc;
+        if (launches == 1) break;
+    }
+    if (!k) return hipErrorCooperativeLaunchTooLarge;
     for (int p0 = 0; p0 < args.planes; p0 += group) {
         EigArgs a = args;
+        a.W = W;
         a.plane0 = p0;
         a.planes = std::min(args.planes, p0 + group);        // planes [p0, a.planes)
         const int n = a.planes - p0;
-        dim3 grid(8 * cdiv(n, 8) * args.W), block(kCoopThreads);
+        dim3 grid(8 * cdiv(n, 8) * W), block(kCoopThreads);
         void *params[] = {&a};
         e = hipLaunchCooperativeKernel((const void *)k, grid, block, params, lds, st);
         if (e != hipSuccess) return e;

@@ -1246,7 +1246,7 @@ hipError_t launch_filter(const ulm_ctx *ctx, float2 *proj, double *eigvals_out, 
         a.status = status;
         a.F = F;
         a.c = c;
-        a.W = split ? eigen_lds_width(F) : eigen_coop_width(F, planes);
+        a.W = split ? eigen_lds_width(F) : 0;                // the other solver chooses its own
         // diagnostic switch: the fenced exchange mode even where a plane's
         // work-groups share one XCD (the results are the same bit for bit)
         a.agent_scope = getenv("ULMPROJ_EIGEN_AGENT_SCOPE") != nullptr;
