@@ -49,6 +49,19 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
     return LIB
 
 
+def build_checks(folder: str) -> None:
+    """Compile the HIP sources in `folder` (test kernels over the library's device headers)
+    to folder/_build/lib<name>.so."""
+    out = os.path.join(folder, "_build")
+    os.makedirs(out, exist_ok=True)
+    for src in sorted(glob.glob(os.path.join(folder, "*.hip"))):
+        lib = os.path.join(out, "lib" + os.path.splitext(os.path.basename(src))[0] + ".so")
+        p = subprocess.Popen([HIPCC] + FLAGS + ["-I", CSRC, src, "-o", lib + ".tmp"],
+                             stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+        _wait((src, p))
+        os.replace(lib + ".tmp", lib)
+
+
 def _wait(item):
     src, p = item
     out, _ = p.communicate()

@@ -7,8 +7,8 @@
 namespace ulm {
 
 // Square roots of N values at once, correctly rounded as sqrtf's: the hardware
-// reciprocal root and one Newton step on the root's residual, which an exhaustive
-// comparison over every float from 2^-96 up finds equal to sqrtf.  Smaller values
+// reciprocal root and one Newton step on the root's residual, which is equal to sqrtf for
+// every float from 2^-96 up (tests/test_gpu_roots.py compares all of them).  Smaller values
 // (zeros among them), infinities and NaN take sqrtf itself, the whole wave's N at
 // once.  6 instructions a value instead of sqrtf's 16.
 template <int N>
