@@ -94,7 +94,8 @@ static_assert(sizeof(NccPeak) == sizeof(ulm_loc_t), "staged in the records' slot
 //      rows in flight during this one), into LDS;
 //   H: thread (row, group of 8 columns) forms the NCC of eight neighbouring
 //      pixels from 8 + 2H sums of each kind, read as 16-byte vectors and used
-//      from registers (3 bytes of LDS read per sum and pixel instead of 4 (2H + 1));
+//      from registers (4 + H bytes of LDS read per kind of sum and pixel instead of
+//      4 (2H + 1): 8 instead of 36 for 9 x 9);
 //   peaks: thread (row, group) tests its eight pixels of the rows whose lower
 //      neighbour is known; offsets in raster order from ballots.
 // Bound by VALU issue: the two passes are 6 (2H + 1) sums a pixel, plus the
@@ -112,6 +113,9 @@ __host__ __device__ inline int ncc_groups(int nu) { return (nu + 2 + 7) / 8; }
 __host__ __device__ inline int ncc_vstride(int nu, int h) { return 8 * ncc_groups(nu) + (2 * h + 7) / 8 * 8; }
 __host__ __device__ inline int ncc_nstride(int nu) { return 8 * ncc_groups(nu) + 4; }
 
+// Five waves a SIMD where the registers nearly allow it: up to 7 x 7 they do, and 9 x 9 is
+// worth three spilled ones (600 images of 250 x 274 220 us, with four waves and none spilled
+// 272; 21,000 images 8.1 and 9.9 ms with the pairing).  From 11 x 11 four.
 template <int H>
 __global__ __launch_bounds__(kNccMaxThreads, H <= 4 ? 5 : 4) void ncc_stream_kernel(
     const float2 *__restrict__ P, float *__restrict__ band_max, NccPeak *__restrict__ staged,

@@ -414,7 +414,8 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 // Pixels of a work-group: rows of 256 bytes (128-byte rows: 777 us where these took 605),
 // but 128 where a thread's second butterfly leaves too few registers for 32 pixels'
 // threads (512 frames, R2 = 32: 824 us with 256-byte rows, 450 so; R2 = 25 still 561
-// against 647).
+// against 647, though its 800 threads leave 128 registers and 14, 15, 18 and 20 beside it
+// spill 3 to 10).
 constexpr int sep_pixels(int r2) { return r2 <= 25 ? 32 : 16; }
 constexpr int sep_threads(int r2) { return (r2 * sep_pixels(r2) + 63) / 64 * 64; }
 

@@ -39,14 +39,14 @@ __device__ inline void pair_of(int pair, int nblk, int &I, int &J) {
 
 // ---------------------------------------------------------------- Gram, FP64 MFMA
 // One work-group: one plane, one 64x64 block pair (I <= J) of C, one chunk of
-// pixels.  Four waves, each a 32x32 quadrant = 2x2 tiles of
-// v_mfma_f64_16x16x4f64.  K = 4 per instruction = 2 pixels x (re, im):
+// pixels.  Four waves, which share the block's 16 x 16 tiles (v_mfma_f64_16x16x4f64): a
+// whole block by 32 x 32 quadrants, fewer tiles in equal numbers.  K = 4 per instruction = 2 pixels x (re, im):
 //   C_re += A . B      with A[f][k], B[k][f'] = (re, im) of pixel p
 //   C_im += A . B'     with B'[k][f'] = (im, -re)
 // FP32 inputs are exact in FP64, so every product is exact and only FP64
 // summation rounds.  Tiles past frame F and those below the diagonal of a diagonal
-// block are not formed, and what is left is dealt evenly to the waves (300 frames: 198
-// tiles of work where 220 were), the pixels in flight come through descriptors, which
+// block are not formed, and what is left is dealt evenly to the waves (300 frames: 190
+// tiles, 200 with those that a last wave repeats, where 220 were), the pixels in flight come through descriptors, which
 // leaves registers for three waves a SIMD: 70 planes of 300 x 68500 39.1 -> 33.0 ms (the
 // products of 190 tiles at the rate of a large FP64 matrix product take 28), 2 planes of 20
 // x 4096 14 -> 7.3 us.
