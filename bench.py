@@ -596,19 +596,28 @@ def profile_das(args):
 
 
 def profile_kernels(args):
-    """One launch each of the clutter filter's Gram in both precision forms and
-    of the CNN localiser on the paper-scale ensemble (for rocprofv3 --pmc runs
-    of the matrix-core counters)."""
+    """One call each of motion estimation, the clutter filter in both precision
+    forms, the NCC and CNN localisers, MB separation, stage 2 of the slab form and
+    a CNN training step on the paper-scale ensemble (for rocprofv3 --pmc runs)."""
     import numpy as np
     import torch
     import paper_2511_21647_amd as ulm
+    from synth import with_blocks
     cfg, ctx, iq = setup("fp64gram")
     proj = ulm.rca_beamform_proj(ctx, iq)
     del iq
+    ulm.ulm_motion_estimate(ctx, ulm.ulm_stage1_slices(ctx), 0, MOTION_MAX_LAG)
+    ctx_s = ulm.Context(with_blocks(cfg, -(-cfg.grid.nv // 8)))
+    ulm.ulm_stage1_slices(ctx_s).copy_(ulm.ulm_stage1_slices(ctx))
+    ulm.rca_beamform_stage2(ctx_s)
+    torch.cuda.synchronize()
+    ctx_s.close()
     ctx_b = ulm.Context(cfg, precision=ulm.ULM_PREC_BF16X3)
     d = proj.clone()
     ulm.svd_clutter_filter(ctx, proj)
     ulm.svd_clutter_filter(ctx_b, d)
+    ulm.ncc_localize(ctx, proj, 4_000_000)
+    ulm.ulm_separate(ctx, proj, SEPARATION_SPEEDS)
     params = torch.from_numpy(np.load(WEIGHTS).astype(np.float32)).cuda()
     cws = ulm.Workspace(ulm.ulm_cnn_localize_workspace_size(ctx_b, 64), "cuda")
     cap = 4_000_000
@@ -616,14 +625,17 @@ def profile_kernels(args):
     count = torch.zeros(1, dtype=torch.int32, device="cuda")
     ulm.ulm_cnn_localize(ctx_b, params, d, cap, ulm.CNN_THRESHOLD, 64, ulm.ULM_CNN_BF16, locs, count,
                          ws=cws)
+    images = ulm.ulm_cnn_images(ctx_b, d)[:16].contiguous()
+    zu = torch.rand((16 * 370, 2), device="cuda") * torch.tensor([250.0, 274.0], device="cuda")
+    ulm.ulm_cnn_gradients(params, images, zu, torch.arange(16, dtype=torch.int32, device="cuda").repeat(370))
     torch.cuda.synchronize()
     ctx_b.close()
     ctx.close()
-    log("profile run done: both Gram forms, the CNN localiser")
+    log("profile run done: one call of each step")
 
 
 MFMA_COUNTERS = ("SQ_VALU_MFMA_BUSY_CYCLES", "GRBM_GUI_ACTIVE", "SQ_INSTS_VALU_MFMA_MOPS_BF16",
-                 "SQ_INSTS_VALU_MFMA_MOPS_F64", "MfmaUtil")
+                 "SQ_INSTS_VALU_MFMA_MOPS_F64", "SQ_INSTS_VALU_MFMA_MOPS_F32", "MfmaUtil")
 
 
 def summarize_mfma(d, out_md, cmd):
@@ -650,7 +662,8 @@ def summarize_mfma(d, out_md, cmd):
             else:
                 a[k] = a.get(k, 0.0) + v
     lines = ["| Kernel | Dispatches | MfmaUtil (%) per dispatch, mean | MFMA-busy cycles (sum) | "
-             "BF16 MFMA flop issued | FP64 MFMA flop issued |", "|---|---|---|---|---|---|"]
+             "BF16 MFMA flop issued | FP64 MFMA flop issued | FP32 MFMA flop issued |",
+             "|---|---|---|---|---|---|---|"]
     for short, a in sorted(agg.items(), key=lambda kv: -kv[1].get("SQ_VALU_MFMA_BUSY_CYCLES", 0)):
         if a.get("SQ_VALU_MFMA_BUSY_CYCLES", 0) <= 0:
             continue
@@ -658,7 +671,8 @@ def summarize_mfma(d, out_md, cmd):
         lines.append(f"| `{short}` | {a['dispatches']} | {util:.1f} | "
                      f"{a.get('SQ_VALU_MFMA_BUSY_CYCLES', 0):.3g} | "
                      f"{512 * a.get('SQ_INSTS_VALU_MFMA_MOPS_BF16', 0):.3g} | "
-                     f"{512 * a.get('SQ_INSTS_VALU_MFMA_MOPS_F64', 0):.3g} |")
+                     f"{512 * a.get('SQ_INSTS_VALU_MFMA_MOPS_F64', 0):.3g} | "
+                     f"{512 * a.get('SQ_INSTS_VALU_MFMA_MOPS_F32', 0):.3g} |")
     text = (f"Command (run from the repository root on one MI355X):\n\n```\n{cmd}\n```\n\n"
             + "\n".join(lines) + "\n")
     with open(out_md, "w") as fh:
