@@ -9,6 +9,12 @@ namespace ulm {
 constexpr int kCoopMaxW = 32;      // work-groups per plane (one barrier flag each)
 constexpr int kPlaceWord = kBarStride - 1;  // per-plane word: bit x set by a work-group on XCC x
 
+// Below this |x|^2 a column's rest is zero.  A covariance of FP32 values that is not zero
+// has a norm of at least 2e-90, so 1e-135 is far below its rounding; but a covariance of low
+// rank (identical frames) leaves a rest that shrinks by 1e-15 a step, and the reciprocals of
+// a reflector's squares overflow where it passes 1e-154.
+constexpr double kNoReflector = 0x1p-900;
+
 struct EigArgs {
     const double2 *C;   // [planes][F][F] covariance (full Hermitian)
     double2 *H;         // [planes][F][F] row k: Householder vector v_k (entries k+1..F-1)

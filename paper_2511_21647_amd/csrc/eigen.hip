@@ -193,11 +193,11 @@ __device__ inline bool reduce_steps(Reduction<NR, NC> &s, const ReductionArgs &a
         const double nrm = wsum(s.nrm_part);
         const double2 alpha = make_double2(lane_value(s.x[MB].x, pl), lane_value(s.x[MB].y, pl));
         double2 tk = make_double2(0.0, 0.0), scale = make_double2(0.0, 0.0);
-        double beta = alpha.x;
-        if (nrm > 0.0 || alpha.y != 0.0) {
+        const double s2 = alpha.x * alpha.x + alpha.y * alpha.y + nrm;
+        double beta = s2 < kNoReflector ? 0.0 : alpha.x;
+        if (s2 >= kNoReflector && (nrm > 0.0 || alpha.y != 0.0)) {
             // with s = |x|: beta = -sign(re alpha) s, tau = (beta - alpha) / beta, and
             // v = x / (alpha - beta)
-            const double s2 = alpha.x * alpha.x + alpha.y * alpha.y + nrm;
             const double is = rsqrt_newton(s2), s1 = s2 * is;
             const double sn = fma(fma(-s1, s1, s2), 0.5 * is, s1);
             beta = -copysign(sn, alpha.x);
