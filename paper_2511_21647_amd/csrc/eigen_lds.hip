@@ -71,10 +71,11 @@ __device__ inline void reflector(const double2 *col, int k, int F, double *red, 
     const double nrm = lds_bsum(nrm_part, red);
     const double2 alpha = col[k + 1];
     tk = make_double2(0.0, 0.0);
-    beta = alpha.x;
+    const double s2 = alpha.x * alpha.x + alpha.y * alpha.y + nrm;
+    beta = s2 < kNoReflector ? 0.0 : alpha.x;
     double2 scale = make_double2(0.0, 0.0);
-    if (nrm > 0.0 || alpha.y != 0.0) {
-        beta = -copysign(sqrt(alpha.x * alpha.x + alpha.y * alpha.y + nrm), alpha.x);
+    if (s2 >= kNoReflector && (nrm > 0.0 || alpha.y != 0.0)) {
+        beta = -copysign(sqrt(s2), alpha.x);
         const double ib = 1.0 / beta;
         tk = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
         const double2 den = make_double2(alpha.x - beta, alpha.y);

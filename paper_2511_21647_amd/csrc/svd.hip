@@ -563,9 +563,10 @@ __global__ __launch_bounds__(kEigThreads) void eigen_kernel(
         nrm = block_sum(nrm, red);
         const double2 alpha = sv[0];
         double2 tk = make_double2(0.0, 0.0);
-        double beta = alpha.x;
-        if (nrm > 0.0 || alpha.y != 0.0) {
-            beta = -copysign(sqrt(alpha.x * alpha.x + alpha.y * alpha.y + nrm), alpha.x);
+        const double s2 = alpha.x * alpha.x + alpha.y * alpha.y + nrm;
+        double beta = s2 < kNoReflector ? 0.0 : alpha.x;
+        if (s2 >= kNoReflector && (nrm > 0.0 || alpha.y != 0.0)) {
+            beta = -copysign(sqrt(s2), alpha.x);
             tk = make_double2((beta - alpha.x) / beta, -alpha.y / beta);
             // scale = 1 / (alpha - beta)
             const double2 den = make_double2(alpha.x - beta, alpha.y);
