@@ -15,6 +15,34 @@ constexpr int kPlaceWord = kBarStride - 1;  // per-plane word: bit x set by a wo
 // a reflector's squares overflow where it passes 1e-154.
 constexpr double kNoReflector = 0x1p-900;
 
+// Inverse iteration for equal eigenvalues (the zeros of a covariance of low rank, frames that
+// repeat).  In decoupled parts of T it returns the start vector's share of each part, or only
+// that of the part whose eigenvalue is nearest by rounding, and the start vectors are of three
+// dimensions: the vectors come out dependent.  So where an eigenvalue equals the one before
+// it within its bracket, the start vector has an independent part, and the shift stands off by
+// more than the parts differ by.
+__device__ inline bool equal_eigenvalues(double a, double b, double tnorm) {
+    return fabs(a - b) <= 0x1p-49 * tnorm;
+}
+__device__ inline double independent_entry(int q, int i) {       // in [-1, 1]
+    unsigned h = (unsigned)q * 0x9e3779b9u + (unsigned)(i + 1) * 0x85ebca6bu;
+    h = (h ^ (h >> 16)) * 0x7feb352du;
+    h = (h ^ (h >> 15)) * 0x846ca68bu;
+    return (double)(int)(h ^ (h >> 16)) * 0x1p-31;
+}
+__device__ inline double start_entry(int q, int i, bool equal) {
+    const double x = 1.0 + 0.37 * sin(0.731 * q + 1.3 * i);
+    return equal ? x + independent_entry(q, i) : x;
+}
+__device__ inline double iteration_shift(double lam, double tnorm, bool equal) {
+    if (tnorm == 0.0) return 0.0;        // T = 0, whose eigenvalues are the bisection's margin
+    return equal ? lam - 0x1p-44 * tnorm : lam;
+}
+// What stands for a pivot of zero (T = 0 takes any).
+__device__ inline double least_pivot(double tnorm, double pivmin) {
+    return tnorm > 0.0 ? 0x1p-52 * tnorm + pivmin : 1.0;
+}
+
 struct EigArgs {
     const double2 *C;   // [planes][F][F] covariance (full Hermitian)
     double2 *H;         // [planes][F][F] row k: Householder vector v_k (entries k+1..F-1)

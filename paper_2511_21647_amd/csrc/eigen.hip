@@ -596,12 +596,13 @@ __global__ __launch_bounds__(kCoopThreads, NR <= 6 ? 2 : 1) void eigen_coop_kern
     for (int vi = wave * W + w; vi < c; vi += ra.nwv) {
         // the start vector, by every lane (the factor and solves below are
         // serial recurrences, run by the first)
-        for (int i = lane; i < F; i += 64) y[i] = 1.0 + 0.37 * sin(0.731 * i + 1.3 * vi);
+        const bool equal = vi > 0 && equal_eigenvalues(ld_c(lam + vi - 1), ld_c(lam + vi), tnorm);
+        for (int i = lane; i < F; i += 64) y[i] = start_entry(i, vi, equal);
         __builtin_amdgcn_wave_barrier();
         double inv = 1.0;                // the last solution's scale, applied as it is read
         if (lane == 0) {
-            const double lm = ld_c(lam + vi);
-            const double tiny = DBL_EPSILON * tnorm + pivmin;
+            const double lm = iteration_shift(ld_c(lam + vi), tnorm, equal);
+            const double tiny = least_pivot(tnorm, pivmin);
             // factor: rows i, i+1 enter step i as (c0, c1 | sub) over (next0, next1);
             // one reciprocal a step, of the pivot
             double c0 = sd[0] - lm, c1 = F > 1 ? se[0] : 0.0;

@@ -712,8 +712,9 @@ __global__ __launch_bounds__(kEigThreads) void eigen_kernel(
     if (t < c) {
         double *u0 = ts + (size_t)t * 6 * F;
         double *u1 = u0 + F, *u2 = u1 + F, *ml = u2 + F, *b = ml + F, *sw_ = b + F;
-        const double lm = lam[t];
-        const double tiny = DBL_EPSILON * tnorm + pivmin;
+        const bool equal = t > 0 && equal_eigenvalues(lam[t - 1], lam[t], tnorm);
+        const double lm = iteration_shift(lam[t], tnorm, equal);
+        const double tiny = least_pivot(tnorm, pivmin);
         for (int i = 0; i < F; ++i) {
             u0[i] = sd[i] - lm;
             u1[i] = (i + 1 < F) ? e[i] : 0.0;
@@ -742,7 +743,7 @@ __global__ __launch_bounds__(kEigThreads) void eigen_kernel(
         }
         if (u0[F - 1] == 0.0) u0[F - 1] = tiny;
         // deterministic start vector
-        for (int i = 0; i < F; ++i) b[i] = 1.0 + 0.37 * sin(0.731 * i + 1.3 * t);
+        for (int i = 0; i < F; ++i) b[i] = start_entry(i, t, equal);
         for (int it = 0; it < 3; ++it) {
             for (int i = 0; i + 1 < F; ++i) {
                 if (sw_[i] != 0.0) { const double tmp = b[i]; b[i] = b[i + 1]; b[i + 1] = tmp; }
