@@ -162,11 +162,14 @@ __global__ __launch_bounds__(256, 4) void stage2_fir_kernel(
 // of 250 x 274 x 300).  Here a (transmit, slab) costs two LDS reads for its taps
 // (staged once per work-group) and eleven reads of the slice tile for 8 x taps x 4
 // FMAs; the next transmit's tile is in flight during it.  The planes, which nothing
-// reads soon, are stored past the caches where their rows are whole 128-byte lines (64 x
-// 64 planes, 9 transmits 109 -> 99 us; 250 x 272, 2 transmits 237 -> 160) or the stores
-// come slowly, with more than four transmits (250 x 274, 9 transmits, 20 frames 520 ->
-// 503 us).  Otherwise parts of lines would reach memory one by one, which the L2 joins
-// (250 x 274, one transmit 357 -> 254 us, four 369 -> 350).  6.1 ms: 4.6 without the stores
+// reads soon, are stored past the caches where their rows are whole 64-byte pieces, the
+// least that memory takes at once (114 x 136 planes, 4 transmits 95 -> 76 us; 250 x 272, 2
+// transmits 237 -> 160), or the stores come slowly, with more than four transmits (250 x 274,
+// 9 transmits, 20 frames 520 -> 503 us).  Otherwise smaller parts would reach memory one by
+// one, which the L2 joins (250 x 274, one transmit 357 -> 254 us, four 369 -> 350; over 149
+// sizes of 1, 2, 3 and 4 transmits 0.70, 0.89, 0.91 and 0.95 of the time, at worst 1.17).
+// Lines a work-group fills stored past the caches and the rest through them lose to the
+// better of the two by up to 26%.  6.1 ms: 4.6 without the stores
 // of 11.5 GB, about 3.5 of FMAs alone.  Groups of 5 to 12 slabs with 4 or 8 rows per thread and 3 to
 // 6 waves per SIMD all take 6.1-7.2 ms.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -309,7 +312,7 @@ hipError_t launch_stage2(const ulm_ctx *ctx, const float2 *slices, float2 *proj,
                         cdiv(g.n_blocks, G);
     if (n_wg > (size_t)INT32_MAX) return hipErrorInvalidConfiguration;
     if (G == kSlabGroup) {
-        const bool narrow = ctx->tab.fir_span <= kSlabSpan, past = g.nu % 16 == 0 || g.n_angles > 4;
+        const bool narrow = ctx->tab.fir_span <= kSlabSpan, past = g.nu % 8 == 0 || g.n_angles > 4;
         hipLaunchKernelGGL(narrow ? (past ? stage2_slab_kernel<kSlabSpan, true> : stage2_slab_kernel<kSlabSpan, false>)
                                   : (past ? stage2_slab_kernel<kSlabMaxSpan, true>
                                           : stage2_slab_kernel<kSlabMaxSpan, false>),
